@@ -101,14 +101,15 @@ void temperature_bounds(const lbm_params& p, const Derived& d, int64_t n, double
     *hi = b + std::fabs(d.dT) + (d.Q > 0 ? rise : 0.0);
 }
 
-// Fills the observables from the results r[0 .. kObsOut) of the observables pass (Nu_hot,
-// Nu_cold, max |u|, sum f', non-finite flag, min T, max T, max |phi p - rho0 cs^2|) and
-// decides the divergence flag (LBM_DIV_* in lbm.h).
+// Fills the observables from the results r[0 .. kObsOut) of the observables pass (the walls'
+// sums of Eq. (38), scaled here, max |u|, sum f', non-finite flag, min T, max T,
+// max |phi p - rho0 cs^2|) and decides the divergence flag (LBM_DIV_* in lbm.h).
 void fill_obs(const lbm_params& p, const Derived& d, int64_t step, const double* r,
               lbm_obs* o) {
     const double n = double(p.nx) * p.ny;
-    o->nu_hot = r[0];
-    o->nu_cold = r[1];
+    const double nu_scale = -(d.L / d.dT) / double(p.ny - 1);
+    o->nu_hot = nu_scale * r[0];
+    o->nu_cold = nu_scale * r[1];
     o->max_speed = r[2];
     o->mass_err = std::fabs(r[3]) / (n * p.rho0);
     o->step = step;
@@ -118,7 +119,8 @@ void fill_obs(const lbm_params& p, const Derived& d, int64_t step, const double*
     double lo, hi;
     temperature_bounds(p, d, step, &lo, &hi);
     int why = 0;
-    if (r[4] != 0.0 || !std::isfinite(r[0]) || !std::isfinite(r[1])) why |= LBM_DIV_NONFINITE;
+    if (r[4] != 0.0 || !std::isfinite(o->nu_hot) || !std::isfinite(o->nu_cold))
+        why |= LBM_DIV_NONFINITE;
     if (!(r[2] <= std::sqrt(d.cs2))) why |= LBM_DIV_SPEED;
     if (!(r[5] >= lo) || !(r[6] <= hi)) why |= LBM_DIV_TEMPERATURE;
     o->why = why;
@@ -242,6 +244,9 @@ Phys<R> make_phys(const lbm_params& p, const Derived& d, double phi_u) {
     return P;
 }
 
+// Partial results of the observables: of the nodes' work-groups, then the walls' sums.
+constexpr int kObsPer = kObsParts * kObserveWG + 2 * kNuWG;
+
 struct Layout {
     size_t state_bytes;   // one population buffer (14 planes)
     size_t off_buf[2];
@@ -272,7 +277,7 @@ Layout make_layout(const lbm_params& p, int64_t nsteps_max, bool med_planes) {
     L.off_med = o;
     if (med_planes) o += align_up(2 * size_t(G.plane) * esz);
     L.off_part = o;
-    o += align_up((kObsParts * kObserveWG + kObsOut) * sizeof(double));
+    o += align_up((kObsPer + kObsOut) * sizeof(double));
     L.off_tape = o;
     if (p.checkpoint_every > 0) {
         const size_t C = size_t(p.checkpoint_every);
@@ -322,7 +327,6 @@ struct lbm_ctx {
     std::vector<Phys<float>> bP32;
     std::vector<Phys<double>> bP64;
     std::vector<long long> boff;      // element offset of each cavity in a state buffer
-    std::vector<double> bLdT;         // L / dT per cavity
     size_t b_state_bytes = 0, b_off_buf[2] = {0, 0}, b_off_cav = 0, b_off_phys = 0;
     size_t b_off_tiles = 0, b_off_part = 0, b_max_tiles = 0;
     int b_wg = 4, b_npt = 1, b_nwg = 0, b_ntiles = 0;   // b_wg: rows per tile
@@ -488,8 +492,8 @@ namespace {
 // ---- batched form ------------------------------------------------------------------------
 
 constexpr int kBatchGraphSteps = 32;   // even: a replay ends on the buffer it started from
-constexpr int kBatchObsWG = 64;        // work-groups of one cavity's observables pass
-constexpr int kBatchObsPer = kObsParts * kBatchObsWG + kObsOut;  // doubles per cavity
+// doubles per cavity: partial results, walls' sums, results
+constexpr int kBatchObsPer = kObsParts * kBatchObsWG + 2 * kNuWG + kObsOut;
 constexpr int kMinTileWidth = 64;      // narrowest tile of any supported launch shape
 
 struct BatchLayout {
@@ -949,12 +953,11 @@ lbm_status setup_ctx(lbm_ctx* c, const lbm_params& p, const Layout& L, int64_t n
 // Observables of the context's current state (see lbm_observables).  Synchronises.
 lbm_status observe_ctx(lbm_ctx* c, lbm_obs* o, void* ux, void* uy, void* p, void* T) {
     double* part = c->part();
-    double* res = part + kObsParts * kObserveWG;
-    const double LdT = c->d.L / c->d.dT;
+    double* res = part + kObsPer;
     hipError_t e = with_types(c->p.dtype, [&](auto st, auto rt) {
         LBM_TYPES(st, rt)
         return launch_observe<S, R>(c->buf(c->cur), c->medp(), c->G, phys<R>(c), pop_layout(c),
-                                    ux, uy, p, T, part, kObserveWG, LdT, res, c->stream);
+                                    ux, uy, p, T, part, res, c->stream);
     });
     if (e != hipSuccess) return hip_fail(e, "observables launch");
     double h[kObsOut];
@@ -1382,7 +1385,6 @@ lbm_status lbm_batch_init(lbm_ctx** out, int32_t n, const lbm_params* p,
         c->bG.push_back(make_geo(p[i]));
         c->bP32.push_back(make_phys<float>(p[i], d, phi_uniform[i]));
         c->bP64.push_back(make_phys<double>(p[i], d, phi_uniform[i]));
-        c->bLdT.push_back(d.L / d.dT);
     }
     // the parameter table in the arithmetic type
     const bool r64 = p[0].dtype != LBM_FP32;
@@ -1450,30 +1452,25 @@ lbm_status lbm_batch_observables(lbm_ctx* c, lbm_obs* o) {
     if (s != LBM_OK) return s;
     if (!o) return fail(LBM_E_INVAL, "null lbm_obs");
     const int n = c->ncav;
-    const size_t esz = storage_bytes(c->p.dtype);
-    double* part0 = (double*)(c->ws + c->b_off_part);
-    const size_t per = kBatchObsPer;
-    char* base = c->ws + c->b_off_buf[c->cur];
-    for (int i = 0; i < n; ++i) {
-        const void* src = base + size_t(c->boff[i]) * esz;
-        double* part = part0 + i * per;
-        double* res = part + kObsParts * kBatchObsWG;
-        hipError_t e = with_types(c->p.dtype, [&](auto st, auto rt) {
-            LBM_TYPES(st, rt)
-            return launch_observe<S, R>(src, nullptr, c->bG[i], bphys<R>(c, i), kPull, nullptr,
-                                        nullptr, nullptr, nullptr, part, kBatchObsWG, c->bLdT[i],
-                                        res, c->stream);
-        });
-        if (e != hipSuccess) return hip_fail(e, "batch observables launch");
-    }
-    std::vector<double> h(size_t(n) * per);
-    HIP_TRY(hipMemcpyAsync(h.data(), part0, h.size() * sizeof(double), hipMemcpyDeviceToHost,
+    // every cavity's partial results, then every cavity's results
+    double* part = (double*)(c->ws + c->b_off_part);
+    double* res = part + size_t(n) * (kBatchObsPer - kObsOut);
+    const void* src = c->ws + c->b_off_buf[c->cur];
+    long long largest = 0;
+    for (const Geo& G : c->bG) largest = std::max(largest, (long long)G.nx * G.ny);
+    hipError_t e = with_types(c->p.dtype, [&](auto st, auto rt) {
+        LBM_TYPES(st, rt)
+        return launch_batch_observe<S, R>(src, batch_table<R>(c), largest, part, res, c->stream);
+    });
+    if (e != hipSuccess) return hip_fail(e, "batch observables launch");
+    std::vector<double> h(size_t(n) * kObsOut);
+    HIP_TRY(hipMemcpyAsync(h.data(), res, h.size() * sizeof(double), hipMemcpyDeviceToHost,
                            c->stream),
             "readback");
     HIP_TRY(hipStreamSynchronize(c->stream), "synchronize");
     bool any = false;
     for (int i = 0; i < n; ++i) {
-        const double* r = h.data() + i * per + kObsParts * kBatchObsWG;
+        const double* r = h.data() + size_t(i) * kObsOut;
         fill_obs(c->bp[i], derive(c->bp[i]), c->step, r, &o[i]);
         any = any || o[i].diverged;
     }
@@ -1487,12 +1484,10 @@ lbm_status lbm_batch_fields(lbm_ctx* c, int32_t i, void* ux, void* uy, void* p, 
     if (i < 0 || i >= c->ncav) return fail(LBM_E_INVAL, "cavity %d of %d", i, c->ncav);
     const size_t esz = storage_bytes(c->p.dtype);
     const void* src = c->ws + c->b_off_buf[c->cur] + size_t(c->boff[i]) * esz;
-    double* part = (double*)(c->ws + c->b_off_part) + size_t(i) * kBatchObsPer;
-    double* res = part + kObsParts * kBatchObsWG;
     hipError_t e = with_types(c->p.dtype, [&](auto st, auto rt) {
         LBM_TYPES(st, rt)
         return launch_observe<S, R>(src, nullptr, c->bG[i], bphys<R>(c, i), kPull, ux, uy, p, T,
-                                    part, kBatchObsWG, c->bLdT[i], res, c->stream);
+                                    nullptr, nullptr, c->stream);
     });
     if (e != hipSuccess) return hip_fail(e, "batch fields launch");
     HIP_TRY(hipStreamSynchronize(c->stream), "synchronize");

@@ -8,9 +8,12 @@
 namespace lbm {
 
 constexpr int kTileX = 256;      // nodes (work-items) per work-group of the step kernel
-constexpr int kObserveWG = 512;  // work-groups of the observables pass
+constexpr int kObserveWG = 508;  // most work-groups of the observables pass over the nodes
+constexpr int kBatchObsWG = 60;  // most of them for one cavity of a batch
+constexpr int kObsThreads = 512; // most work-items per work-group of the observables pass
+constexpr int kNuWG = 12;        // most work-groups of the walls' Nusselt sums
 constexpr int kObsParts = 6;     // partial results per work-group of the observables pass
-constexpr int kObsOut = 2 + kObsParts;  // results of the observables pass (Nu_hot, Nu_cold, ...)
+constexpr int kObsOut = 2 + kObsParts;  // results of the observables pass (Nu sums, ...)
 constexpr int kPitchAlign = 64;  // row pitch in elements
 // Elements between the end of one plane's rows and the start of the next (4 KiB + 128 B in
 // FP32).  Without it the planes of a 4096-wide power-of-two grid lie exactly 64 MiB apart and
@@ -106,11 +109,13 @@ hipError_t launch_tb2_step(const void* src, void* dst, const void* med, const Ge
 template <typename S, typename R>
 hipError_t launch_aa_step(void* buf, const void* med, const Geo& G, const Phys<R>& P,
                           int parity, hipStream_t s);
-// layout: the PopLayout form the state is in
+// layout: the PopLayout form the state is in.  Fields (each may be NULL), and with part (room for
+// kObsParts * kObserveWG + 2 * kNuWG doubles) the kObsOut results at out: the unscaled sums of Eq. (38) at the
+// west and east walls, max |u|, sum f', non-finite flag, min T, max T, max |phi p - rho0 cs^2|.
 template <typename S, typename R>
 hipError_t launch_observe(const void* src, const void* med, const Geo& G, const Phys<R>& P,
                           int layout, void* ux, void* uy, void* p, void* T, double* part,
-                          int nparts, double L_over_dT, double* out, hipStream_t s);
+                          double* out, hipStream_t s);
 template <typename S, typename R>
 hipError_t launch_stream_function(const void* src, const void* med, const Geo& G,
                                   const Phys<R>& P, int layout, void* psi, hipStream_t s);
@@ -159,6 +164,12 @@ hipError_t launch_batch_tb2(const void* src, void* dst, const BatchTable<R>& T, 
 // Queries the batched two-step kernel's resident set once (call outside graph capture)
 template <typename S, typename R>
 void prepare_batch_tb2();
+
+// Observables of every cavity (no fields): results of cavity i at out[kObsOut * i]; part has room
+// for kObsParts * kBatchObsWG + 2 * kNuWG doubles per cavity; largest: nodes of the largest one.
+template <typename S, typename R>
+hipError_t launch_batch_observe(const void* src, const BatchTable<R>& T, long long largest,
+                                double* part, double* out, hipStream_t s);
 
 // rows: rows per tile (work-group = 64 * rows work-items); nodes_x: 64-node segments per
 // work-item along x; nwg >= ntiles: one tile per work-group, else chunked persistent.
