@@ -93,22 +93,70 @@ struct Mac {
 // wanted it is written out (fma), the same in every kernel.  Products by 2, 4, 0.25 and 0.5
 // are exact, so fma(2, a, b) rounds like 2 * a + b did.
 //
+// recip, quotient, root: correctly rounded 1/b, a/b and sqrt(x) from the hardware's approximations
+// by Newton steps with fused multiply-adds (Markstein, IBM J. Res. Dev. 34 (1990)), without the
+// scaling that the compiler's expansions spend on operands at the ends of the exponent range,
+// which the step does not have (den >= 1, l0 >= 1/2), and with one reciprocal for both of Eq.
+// (21)'s quotients.  div_fixup puts in the IEEE result for zeros, infinities and NaNs.  In FP32
+// one step each gives 1/b for every mantissa of b and sqrt(x) for every x of two binades (both
+// enumerated on gfx950), and with a correctly rounded reciprocal the quotient is correct wherever
+// its residual does not underflow (|a| above 2^-100); in FP64 2e8 random operands agree with / and
+// sqrt.  Vector instruction slots per node (4 cycles each): FP32 31 to 21, FP64 80 to 55.
+__device__ __forceinline__ float recip(float b) {
+    const float r = __builtin_amdgcn_rcpf(b);
+    return fma(fma(-b, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double recip(double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(r, fma(-b, r, 1.0), r);
+    return fma(r, fma(-b, r, 1.0), r);
+}
+__device__ __forceinline__ float div_special(float q, float b, float a) {
+    return __builtin_amdgcn_div_fixupf(q, b, a);
+}
+__device__ __forceinline__ double div_special(double q, double b, double a) {
+    return __builtin_amdgcn_div_fixup(q, b, a);
+}
+// a / b with r = recip(b)
+template <typename R>
+__device__ __forceinline__ R quotient(R a, R b, R r) {
+    const R q = a * r;
+    return div_special(fma(fma(-b, q, a), r, q), b, a);
+}
+// 1 / b for any b (recip leaves a NaN at b = 0 or infinity)
+__device__ __forceinline__ float reciprocal(float b) { return div_special(recip(b), b, 1.0f); }
+__device__ __forceinline__ double reciprocal(double b) { return quotient(1.0, b, recip(b)); }
+__device__ __forceinline__ float root(float x) {
+    const float r = __builtin_amdgcn_rsqf(x);
+    const float g = x * r;
+    return div_special(fma(fma(-g, g, x), 0.5f * r, g), 1.0f, x);
+}
+__device__ __forceinline__ double root(double x) {
+    const double r = __builtin_amdgcn_rsq(x);
+    const double g = x * r, h = 0.5 * r;
+    const double e = fma(-h, g, 0.5);
+    const double g1 = fma(g, e, g);
+    return div_special(fma(fma(-g1, g1, x), fma(h, e, h), g1), 1.0, x);
+}
+
 // rsq_1ulp, sqrt_1ulp: in FP32 the hardware reciprocal square root and square root (within
-// 1 ulp) instead of the correctly rounded sequences (~15 instructions each).  They are used
-// only where one rounding more cannot act as a common gain: the medium coefficients of a
-// per-node medium (Eq. (5), different at every node), |v| inside Eq. (21)'s root (a small
-// correction to l0^2) and |u| in Eq. (4)'s Forchheimer term.  FP64 keeps sqrt.
+// 1 ulp) instead of the correctly rounded sequences.  They are used only where one rounding more
+// cannot act as a common gain: the medium coefficients of a per-node medium (Eq. (5), different
+// at every node), |v| inside Eq. (21)'s root (a small correction to l0^2) and |u| in Eq. (4)'s
+// Forchheimer term.  FP64 keeps the correctly rounded root.
 __device__ __forceinline__ float rsq_1ulp(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsq_1ulp(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double rsq_1ulp(double x) {
+    return reciprocal(root(x));
+}
 __device__ __forceinline__ float sqrt_1ulp(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double sqrt_1ulp(double x) { return sqrt(x); }
+__device__ __forceinline__ double sqrt_1ulp(double x) { return root(x); }
 
 template <typename R>
 __device__ __forceinline__ Med<R> medium_from(R phi, R K, const Phys<R>& P) {
     Med<R> m;
     const R rK = rsq_1ulp(K);
     m.phi = phi;
-    m.inv_phi = R(1) / phi;
+    m.inv_phi = reciprocal(phi);
     m.c_lin = phi * P.nu * (rK * rK);
     m.c_nl = P.forch ? R(kErgun) * rsq_1ulp(phi) * rK : R(0);
     return m;
@@ -221,13 +269,14 @@ __device__ __forceinline__ Vel<R> velocity(const R f[9], const R g[5], const Med
     v.l1 = R(0.5) * md.c_nl;
     v.vv = fma(v.vx, v.vx, v.vy * v.vy);
     v.vm = sqrt_1ulp(v.vv);
-    v.q = sqrt(fma(v.l0, v.l0, v.l1 * v.vm));
+    v.q = root(fma(v.l0, v.l0, v.l1 * v.vm));
     v.den = v.l0 + v.q;
     // divide rather than multiply by a rounded reciprocal: in a uniform medium the denominator
     // is nearly the same at every node, so the reciprocal's rounding would act as one common
     // gain on the momentum, step after step
-    v.ux = v.vx / v.den;
-    v.uy = v.vy / v.den;
+    const R r = recip(v.den);
+    v.ux = quotient(v.vx, v.den, r);
+    v.uy = quotient(v.vy, v.den, r);
     v.uu = fma(v.ux, v.ux, v.uy * v.uy);
     v.um = sqrt_1ulp(v.uu);
     v.drag = fma(md.c_nl, v.um, md.c_lin);
