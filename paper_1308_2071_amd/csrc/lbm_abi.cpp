@@ -403,35 +403,24 @@ hipError_t advance(lbm_ctx* c, int from, hipStream_t s) {
     });
 }
 
-// k > 1 steps in one launch from buffer `from` (pull layout only): the two- and three-step
-// kernels for k = 2 and 3, the tiles in LDS for k = kTileSteps or kTinyTileSteps.
+// k > 1 steps in one launch from buffer `from` (pull layout only).
 hipError_t advance_k(lbm_ctx* c, int k, int from, hipStream_t s) {
     return with_types(c->p.dtype, [&](auto st, auto rt) {
         LBM_TYPES(st, rt)
-        if (k == 2)
-            return launch_tb2_step<S, R>(c->buf(from), c->buf(1 - from), c->medp(), c->G,
-                                         phys<R>(c), s);
-        if (k == 3)
-            return launch_tb3_step<S, R>(c->buf(from), c->buf(1 - from), c->medp(), c->G,
-                                         phys<R>(c), s);
         return launch_tile_step<S, R>(c->buf(from), c->buf(1 - from), c->medp(), c->G,
                                       phys<R>(c), k, s);
     });
 }
 
 // Time steps per launch of the time loop: one with the AA layout; steps_per_launch when it
-// asks for 1, 2, 3, kTileSteps or kTinyTileSteps; by default three (FP32) or two where that is
-// measured to pay, else the tiles in LDS where a form of them does, else one.  With a tape,
-// launches of several steps run only between checkpoints (lbm_step).
+// asks for 1, 2, 3, kTileSteps or kTinyTileSteps; by default what is measured to pay.  With a
+// tape, launches of several steps run only between checkpoints (lbm_step).
 int launch_steps(const lbm_ctx* c) {
     if (c->p.layout != LBM_LAYOUT_PULL) return 1;
     if (c->p.steps_per_launch != 0) return c->p.steps_per_launch;
     return with_types(c->p.dtype, [&](auto st, auto rt) {
         LBM_TYPES(st, rt)
-        if (tb3_pays<S, R>(c->G, c->med)) return 3;
-        if (tb2_pays<S, R>(c->G, c->med)) return 2;
-        const int t = tile_steps<S, R>(c->G, c->med);
-        return t > 0 ? t : 1;
+        return default_steps<S, R>(c->G, c->med);
     });
 }
 
@@ -927,9 +916,8 @@ lbm_status setup_ctx(lbm_ctx* c, const lbm_params& p, const Layout& L, int64_t n
     c->P64 = make_phys<double>(p, c->d, c->phi_u);
     const double g0 = (1.0 - p.varpi) / 5.0 * (p.T_init - c->d.T0);
     const double g1 = (4.0 + p.varpi) / 20.0 * (p.T_init - c->d.T0);
-    hipError_t e = with_types(p.dtype, [&](auto st, auto rt) {
-        LBM_TYPES(st, rt)
-        prepare_tb2<S, R>();
+    hipError_t e = with_types(p.dtype, [&](auto st, auto) {
+        using S = typename decltype(st)::type;
         hipError_t e1 = hipSuccess;
         if (med) {
             char* mp = c->ws + L.off_med;
@@ -1503,19 +1491,11 @@ lbm_status lbm_step_shape(const lbm_ctx* c, int32_t* out) {
     out[1] = c->p.layout;
     out[2] = 0;
     out[3] = (c->G.nx + kTileX - 1) / kTileX * c->G.ny;
-    if (k == kTileSteps || k == kTinyTileSteps) {
-        const int ts = tile_side(k);
-        out[2] = ts;
-        out[3] = (c->G.nx + ts - 1) / ts * ((c->G.ny + ts - 1) / ts);
-    }
-    if (k == 2 || k == 3)
+    if (k > 1)
         (void)with_types(c->p.dtype, [&](auto st, auto rt) {
             LBM_TYPES(st, rt)
-            int rows = 0, nseg = 0, nwg = 0;
-            if (k == 2)
-                tb2_shape<S, R>(c->G, c->med, &rows, &nwg);
-            else
-                tb3_shape<S, R>(c->G, c->med, &rows, &nseg, &nwg);
+            int rows = 0, nwg = 0;
+            tile_shape<S, R>(c->G, k, &rows, &nwg);
             out[2] = rows;
             out[3] = nwg;
             return 0;

@@ -25,12 +25,8 @@ constexpr int kPlanePad = 1056;
 // Elements per plane: ny rows of the pitch, then the pad.
 inline long long plane_elems(long long pitch, long long ny) { return pitch * ny + kPlanePad; }
 
-// Two steps per launch: columns a wavefront's strip writes, strips per work-group, the number
-// of resident-set rounds the segment height aims for, and the shortest segment.
+// Two steps per launch of the batch: columns a wavefront's strip writes.
 constexpr int kTbCols = 62;
-constexpr int kTbWaves = 4;
-constexpr int kTbRounds = 12;
-constexpr int kTbMinRows = 6;
 // The shortest segment the batch's autotuner tries.
 constexpr int kBatchTbMinRows = 2;
 // Minimum wavefronts per SIMD the two-step kernels are compiled for: in FP32 four, the
@@ -41,18 +37,11 @@ constexpr int tb_min_waves() {
     return sizeof(S) == 4 && sizeof(R) == 4 ? 4 : 1;
 }
 
-// Several steps per launch on small grids (lbm_tile.hip), in two forms of the same region
-// (a tile, a halo as wide as the steps, and one node more at a wall: 25 x 25 nodes at most):
-// 16 x 16 tiles advanced four steps, and on the smallest grids 8 x 8 tiles advanced eight.
+// Tile side and steps per launch of the forms for small grids (lbm_tile.hip).
 constexpr int kTileSide = 16;
 constexpr int kTileSteps = 4;
 constexpr int kTinyTileSide = 8;
 constexpr int kTinyTileSteps = 8;
-constexpr int kTileThreads = 640;   // one work-item per node of the largest region (25^2)
-static_assert(kTileSide + 2 * kTileSteps == kTinyTileSide + 2 * kTinyTileSteps,
-              "both tile forms share one region size");
-// Tile side of the form that takes k steps per launch
-constexpr int tile_side(int k) { return k == kTinyTileSteps ? kTinyTileSide : kTileSide; }
 
 // The two-step kernels address a state (the 14 planes) through raw buffer descriptors and drop
 // stores through an offset of 2^31 past them, so a descriptor covers less than 2^31 bytes: one
@@ -65,7 +54,6 @@ inline int tb2_descs(const Geo& G, size_t elem_bytes) {
     if (kPlanes / 2 * pb < (1ull << 31)) return 2;
     return 0;
 }
-inline bool tb2_fits(const Geo& G, size_t elem_bytes) { return tb2_descs(G, elem_bytes) > 0; }
 
 // Launchers take S, the storage type of populations and medium planes, and R, the arithmetic
 // type; instantiated for (float, float), (double, double) and (float, double).
@@ -73,38 +61,17 @@ inline bool tb2_fits(const Geo& G, size_t elem_bytes) { return tb2_descs(G, elem
 template <typename S, typename R>
 hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G,
                        const Phys<R>& P, hipStream_t s);
-// Queries the device once for the two-step kernel's launch shape (call outside graph capture)
+// Steps per launch of the time loop that are fastest for this grid and these types
 template <typename S, typename R>
-void prepare_tb2();
-// Whether two steps per launch are faster than one for this grid and these types
-template <typename S, typename R>
-bool tb2_pays(const Geo& G, bool per_node_medium);
-// Steps per launch of the tile form that is fastest for this grid and these types, if one beats
-// a step per launch (kTileSteps or kTinyTileSteps), else 0
-template <typename S, typename R>
-int tile_steps(const Geo& G, bool per_node_medium);
-// k (kTileSteps or kTinyTileSteps) steps of the pull layout from src to dst, each tile of the
-// grid advanced in LDS
+int default_steps(const Geo& G, bool per_node_medium);
+// k (2, 3, kTileSteps or kTinyTileSteps) steps of the pull layout in one launch from src to dst,
+// each tile of the grid advanced in LDS
 template <typename S, typename R>
 hipError_t launch_tile_step(const void* src, void* dst, const void* med, const Geo& G,
                             const Phys<R>& P, int k, hipStream_t s);
-// Three steps per launch (FP32 storage and arithmetic only; hipErrorInvalidValue otherwise, or
-// for a state of 2 GiB or more): whether they are faster than two for this grid; rows per
-// segment, segments and work-groups per launch; the launch, src (step n) to dst (step n + 3)
+// Rows per tile and work-groups per launch of that kernel
 template <typename S, typename R>
-bool tb3_pays(const Geo& G, bool per_node_medium);
-template <typename S, typename R>
-void tb3_shape(const Geo& G, bool per_node_medium, int* rows, int* nseg, int* nwg);
-template <typename S, typename R>
-hipError_t launch_tb3_step(const void* src, void* dst, const void* med, const Geo& G,
-                           const Phys<R>& P, hipStream_t s);
-// Rows per segment and work-groups per launch of the two-step kernel
-template <typename S, typename R>
-void tb2_shape(const Geo& G, bool per_node_medium, int* rows, int* nwg);
-// Two pull-layout steps in one launch, src (step n) to dst (step n + 2)
-template <typename S, typename R>
-hipError_t launch_tb2_step(const void* src, void* dst, const void* med, const Geo& G,
-                           const Phys<R>& P, hipStream_t s);
+void tile_shape(const Geo& G, int k, int* rows, int* nwg);
 // AA-pattern step in place; parity 0: the state is in the kAAOpp form, 1: kAAOwn
 template <typename S, typename R>
 hipError_t launch_aa_step(void* buf, const void* med, const Geo& G, const Phys<R>& P,

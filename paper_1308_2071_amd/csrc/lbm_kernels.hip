@@ -1,10 +1,8 @@
-// lbm_kernels.hip -- single-cavity kernels: the time step (one step per launch, two steps per
-// launch, and the in-place AA-layout forms), the observables pass with the wall Nusselt sums
+// lbm_kernels.hip -- single-cavity kernels: the time step (one step per launch, and the in-place
+// AA-layout forms), the observables pass with the wall Nusselt sums
 // (also over a batch), the stream function and state initialisation.
 #include "lbm_device.hpp"
 #include "lbm_internal.hpp"
-#include "lbm_tb2.hpp"
-#include "lbm_tb3.hpp"
 
 namespace lbm {
 
@@ -64,54 +62,6 @@ __global__ __launch_bounds__(kTileX) void aa_step_kernel(S* __restrict__ buf,
                                    });
     collide<R>(f, g, m, md, P);
     aa_store<S, R, L>(buf, G, x, y, f, g);
-}
-
-template <typename S, typename R, bool PN, int NDESC>
-__global__ __launch_bounds__(64 * kTbWaves, (tb_min_waves<S, R>())) void tb2_step_kernel(const S* __restrict__ src,
-                                                                 S* __restrict__ dst,
-                                                                 const S* __restrict__ med,
-                                                                 Geo G, Phys<R> P, int nstrips,
-                                                                 int rows, int chunk) {
-    // A work-group holds kTbWaves adjacent strips of one row segment, kept in step by a
-    // barrier per row, so that the cache lines the neighbouring strips share are used while
-    // resident.
-    const int wg = tb_logical_group(chunk);
-    const int ngrp = (nstrips + kTbWaves - 1) / kTbWaves;
-    const int strip = (wg % ngrp) * kTbWaves + (threadIdx.x >> 6), seg = wg / ngrp;
-    tb2_segment<S, R, PN, NDESC>(src, dst, med, G, P, strip, strip < nstrips, seg, rows);
-}
-
-// Three steps per launch (FP32): a work-group holds kTb3Waves adjacent strips of one row
-// segment, each with its own ring of step n+2 rows in LDS, kept in step by a barrier per row.
-// Segments alternate their sweep direction, except that the segment at a south wall sweeps
-// forwards and the one at a north wall backwards.  The nseg segments split the rows evenly: the
-// first `extra` have rows + 1 rows, the others rows, so that no work-group runs long.
-template <typename S, typename R, bool PN>
-__global__ __launch_bounds__(64 * kTb3Waves, 3) void tb3_step_kernel(const S* __restrict__ src,
-                                                                   S* __restrict__ dst,
-                                                                   const S* __restrict__ med,
-                                                                   Geo G, Phys<R> P, int nstrips,
-                                                                   int rows, int extra, int nseg,
-                                                                   int chunk) {
-    __shared__ S ring[kTb3Waves * kTb3Ring];
-    const int wg = tb_logical_group(chunk);
-    const int ngrp = (nstrips + kTb3Waves - 1) / kTb3Waves;
-    const int w = int(threadIdx.x) >> 6;
-    const int strip = (wg % ngrp) * kTb3Waves + w, seg = wg / ngrp;
-    const int ylo = seg * rows + min(seg, extra);
-    const int yhi = ylo + rows + (seg < extra ? 1 : 0);
-    const bool rev = (G.wallN && seg == nseg - 1) || (!(G.wallS && seg == 0) && (seg & 1));
-    S* const my = ring + w * kTb3Ring;
-    // The relaxation constants from LDS: held in scalar registers across the row loop they
-    // overflow the scalar register file, and reloading spilled ones costs a vector instruction
-    // each (v_readlane), some 80 per row; from LDS they live in vector registers (1.6 % faster).
-    __shared__ Phys<R> sP;
-    if (threadIdx.x == 0) sP = P;
-    __syncthreads();
-    if (rev)
-        tb3_sweep<S, R, PN, true>(src, dst, med, G, sP, strip, strip < nstrips, ylo, yhi, my);
-    else
-        tb3_sweep<S, R, PN, false>(src, dst, med, G, sP, strip, strip < nstrips, ylo, yhi, my);
 }
 
 // Maximum and minimum that propagate a NaN (fmax and fmin would drop it), so that a
@@ -490,204 +440,6 @@ hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G
     return hipGetLastError();
 }
 
-
-// Work-groups of the two-step kernel resident on the device at once (0 if unknown).
-template <typename S, typename R, bool PN>
-int tb_resident_groups() {
-    static const int n = [] {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tb2_step_kernel<S, R, PN, 1>,
-                                                         64 * kTbWaves, 0) != hipSuccess)
-            return 0;
-        return cus * per_cu;
-    }();
-    return n;
-}
-
-// Rows per segment of the two-step kernel.  Each segment reads the intermediate step's two
-// halo rows and one row past its end on top of its own rows; neighbouring segments, which sweep
-// towards each other, find some of those rows in L2.  Longer segments fetch less but live
-// longer, and the launch's tail, in which the last work-groups finish on a partly idle device,
-// grows with them.  Measured on the 4096^2 workload (FP32, MLUPS; fetched bytes over one read
-// of the 16 planes): 5 rows 70.6k, 6 rows (12 rounds of the resident set) 71.6k and 1.36x,
-// 11 rows 1.29x, 17 rows 1.24x, 23 rows (3 rounds) 65.2k and 1.21x, 35 rows 1.17x, 69 rows
-// (one round) 1.12x.  (Work-groups of 8 strips instead of 4 measured the same in FP32 and 5 %
-// slower in FP64, 16 strips 5 % slower; a work-group of two vertically adjacent segments, 8
-// wavefronts, fetched and ran the same as two work-groups of one.)
-int tb_rows(const Geo& G, int nstrips, int resident) {
-    const int ngrp = (nstrips + kTbWaves - 1) / kTbWaves;
-    const int nseg = resident > 0 ? max(1, kTbRounds * resident / ngrp) : 1;
-    return max(kTbMinRows, (G.ny + nseg - 1) / nseg);
-}
-
-template <typename S, typename R>
-int tb_resident(bool per_node_medium) {
-    return per_node_medium ? tb_resident_groups<S, R, true>()
-                           : tb_resident_groups<S, R, false>();
-}
-
-// Work-groups of the three-step kernel resident on the device at once (0 if unknown).
-template <typename S, typename R, bool PN>
-int tb3_resident_groups() {
-    static const int n = [] {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tb3_step_kernel<S, R, PN>,
-                                                         64 * kTb3Waves, 0) != hipSuccess)
-            return 0;
-        return cus * per_cu;
-    }();
-    return n;
-}
-
-template <typename S, typename R>
-int tb3_resident(bool per_node_medium) {
-    return per_node_medium ? tb3_resident_groups<S, R, true>()
-                           : tb3_resident_groups<S, R, false>();
-}
-
-// Rows per segment of the three-step kernel (the least height: the segments split the rows
-// evenly, so some take one more), segments and work-groups per launch.  On a walled y axis there
-// are at least two segments, so that each walled end is where a segment's sweep starts.  A
-// segment recomputes two rows of step n+1 and one of step n+2 beyond each end, so it is at least
-// kTb3MinRows high; measured on the 4096^2 FP32 cavity, 16 rows (six rounds of the resident set)
-// beat 8 and 32 by 6 %, and on 2048^2, 8 rows beat 4 by 7 %.
-constexpr int kTb3Rounds = 6;
-constexpr int kTb3MinRows = 8;
-void tb3_shape_rows(const Geo& G, int resident, int* rows, int* nseg, int* nwg) {
-    const int nstrips = (G.nx + kTb3Cols - 1) / kTb3Cols;
-    const int ngrp = (nstrips + kTb3Waves - 1) / kTb3Waves;
-    const int want = resident > 0 ? max(1, kTb3Rounds * resident / ngrp) : 1;
-    const int r = max(kTb3MinRows, (G.ny + want - 1) / want);
-    int n = max(1, G.ny / r);
-    if (G.wallS && n < 2) n = 2;
-    *rows = G.ny / n;
-    *nseg = n;
-    *nwg = ngrp * n;
-}
-
-// Queries the resident set of the two-step kernel once, outside any graph capture.
-template <typename S, typename R>
-void prepare_tb2() {
-    (void)tb_resident<S, R>(true);
-    (void)tb_resident<S, R>(false);
-    if constexpr (std::is_same<S, float>::value && std::is_same<R, float>::value) {
-        (void)tb3_resident<S, R>(true);
-        (void)tb3_resident<S, R>(false);
-    }
-}
-
-// Whether two steps per launch beat one.  Measured (fused / single MLUPS, per-node medium):
-//   FP32           4096^2 1.38, 2048^2 1.26, 1024^2 1.17, 512^2 0.52, 256^2 0.34
-//   FP64           4096^2 1.53, 2048^2 1.31, 1024^2 1.19, 512^2 0.58
-//   FP32 storage,  4096^2 1.04, 2048^2 0.83, 1024^2 0.64 (225 registers, 2 waves per SIMD)
-//   FP64 arithmetic
-// On small grids the few long row loops are latency-bound.  With equal types the kernel fuses
-// when its work-groups at 16-row segments number at least a quarter of the resident set, with
-// FP64 arithmetic on FP32 storage when they number eight times the resident set; and only for
-// a state whose halves (7 planes) are below 2 GiB, which two buffer descriptors address.
-template <typename S, typename R>
-bool tb2_pays(const Geo& G, bool per_node_medium) {
-    if (!tb2_fits(G, sizeof(S))) return false;
-    const int resident = tb_resident<S, R>(per_node_medium);
-    const int nstrips = (G.nx + kTbCols - 1) / kTbCols;
-    const long long groups =
-        (long long)((nstrips + kTbWaves - 1) / kTbWaves) * ((G.ny + 15) / 16);
-    if (resident <= 0) return false;
-    return std::is_same<S, R>::value ? 4 * groups >= resident : groups >= 8LL * resident;
-}
-
-// Whether three steps per launch beat two (FP32 storage and arithmetic, a state below 2 GiB).
-// Measured (three / two steps per launch, FP32; per-node and uniform medium alike):
-//   4096^2 1.20 (16-row segments), 2048^2 1.02 (8 rows), 1024^2 0.82
-// (at 512^2 the tiles in LDS beat both).  It pays when segments of kTb3MinRows rows make at
-// least three rounds of the resident set.
-template <typename S, typename R>
-bool tb3_pays(const Geo& G, bool per_node_medium) {
-    if constexpr (std::is_same<S, float>::value && std::is_same<R, float>::value) {
-        if (tb2_descs(G, sizeof(S)) != 1) return false;
-        const int resident = tb3_resident<S, R>(per_node_medium);
-        if (resident <= 0) return false;
-        const long long ngrp = ((G.nx + kTb3Cols - 1) / kTb3Cols + kTb3Waves - 1) / kTb3Waves;
-        return ngrp * (G.ny / kTb3MinRows) >= 3LL * resident;
-    } else {
-        (void)G, (void)per_node_medium;
-        return false;
-    }
-}
-
-template <typename S, typename R>
-void tb2_shape(const Geo& G, bool per_node_medium, int* rows, int* nwg) {
-    const int nstrips = (G.nx + kTbCols - 1) / kTbCols;
-    *rows = tb_rows(G, nstrips, tb_resident<S, R>(per_node_medium));
-    *nwg = (nstrips + kTbWaves - 1) / kTbWaves * ((G.ny + *rows - 1) / *rows);
-}
-
-template <typename S, typename R>
-hipError_t launch_tb2_step(const void* src, void* dst, const void* med, const Geo& G,
-                           const Phys<R>& P, hipStream_t s) {
-    const int ndesc = tb2_descs(G, sizeof(S));
-    if (ndesc == 0) return hipErrorInvalidValue;
-    const int nstrips = (G.nx + kTbCols - 1) / kTbCols;
-    int rows = 0, nwg = 0;
-    tb2_shape<S, R>(G, med != nullptr, &rows, &nwg);
-    // XCD chunks of one XCD's resident work-groups (the resident set over 8 XCDs)
-    const int chunk = max(1, tb_resident<S, R>(med != nullptr) / 8);
-    if (med && ndesc == 1)
-        tb2_step_kernel<S, R, true, 1><<<nwg, 64 * kTbWaves, 0, s>>>(
-            (const S*)src, (S*)dst, (const S*)med, G, P, nstrips, rows, chunk);
-    else if (med)
-        tb2_step_kernel<S, R, true, 2><<<nwg, 64 * kTbWaves, 0, s>>>(
-            (const S*)src, (S*)dst, (const S*)med, G, P, nstrips, rows, chunk);
-    else if (ndesc == 1)
-        tb2_step_kernel<S, R, false, 1><<<nwg, 64 * kTbWaves, 0, s>>>(
-            (const S*)src, (S*)dst, nullptr, G, P, nstrips, rows, chunk);
-    else
-        tb2_step_kernel<S, R, false, 2><<<nwg, 64 * kTbWaves, 0, s>>>(
-            (const S*)src, (S*)dst, nullptr, G, P, nstrips, rows, chunk);
-    return hipGetLastError();
-}
-
-template <typename S, typename R>
-void tb3_shape(const Geo& G, bool per_node_medium, int* rows, int* nseg, int* nwg) {
-    if constexpr (std::is_same<S, float>::value && std::is_same<R, float>::value)
-        tb3_shape_rows(G, tb3_resident<S, R>(per_node_medium), rows, nseg, nwg);
-    else
-        *rows = *nseg = *nwg = 0;
-}
-
-template <typename S, typename R>
-hipError_t launch_tb3_step(const void* src, void* dst, const void* med, const Geo& G,
-                           const Phys<R>& P, hipStream_t s) {
-    if constexpr (std::is_same<S, float>::value && std::is_same<R, float>::value) {
-        if (tb2_descs(G, sizeof(S)) != 1) return hipErrorInvalidValue;
-        const int nstrips = (G.nx + kTb3Cols - 1) / kTb3Cols;
-        int rows = 0, nseg = 0, nwg = 0;
-        tb3_shape<S, R>(G, med != nullptr, &rows, &nseg, &nwg);
-        // every segment holds at least one row (its sweep loop runs until it passes the last),
-        // and on a walled y axis two segments of at least two
-        if (nseg < 1 || nseg > G.ny || (G.wallS && (nseg < 2 || rows < 2)))
-            return hipErrorInvalidValue;
-        const int extra = G.ny - rows * nseg;   // segments one row taller
-        const int chunk = max(1, tb3_resident<S, R>(med != nullptr) / 8);
-        if (med)
-            tb3_step_kernel<S, R, true><<<nwg, 64 * kTb3Waves, 0, s>>>(
-                (const S*)src, (S*)dst, (const S*)med, G, P, nstrips, rows, extra, nseg, chunk);
-        else
-            tb3_step_kernel<S, R, false><<<nwg, 64 * kTb3Waves, 0, s>>>(
-                (const S*)src, (S*)dst, nullptr, G, P, nstrips, rows, extra, nseg, chunk);
-        return hipGetLastError();
-    } else {
-        (void)src, (void)dst, (void)med, (void)G, (void)P, (void)s;
-        return hipErrorInvalidValue;
-    }
-}
-
 // parity 0: the state is in the kAAOpp form (even step count); 1: kAAOwn (odd)
 template <typename S, typename R>
 hipError_t launch_aa_step(void* buf, const void* med, const Geo& G, const Phys<R>& P,
@@ -808,15 +560,6 @@ hipError_t launch_pitch_copy(void* dst, const void* src, const Geo& G, double v,
                                           const Phys<R>&, hipStream_t);                          \
     template hipError_t launch_aa_step<S, R>(void*, const void*, const Geo&, const Phys<R>&,     \
                                              int, hipStream_t);                                  \
-    template hipError_t launch_tb2_step<S, R>(const void*, void*, const void*, const Geo&,       \
-                                              const Phys<R>&, hipStream_t);                      \
-    template void prepare_tb2<S, R>();                                                           \
-    template bool tb2_pays<S, R>(const Geo&, bool);                                              \
-    template void tb2_shape<S, R>(const Geo&, bool, int*, int*);                                 \
-    template bool tb3_pays<S, R>(const Geo&, bool);                                              \
-    template void tb3_shape<S, R>(const Geo&, bool, int*, int*, int*);                           \
-    template hipError_t launch_tb3_step<S, R>(const void*, void*, const void*, const Geo&,       \
-                                              const Phys<R>&, hipStream_t);                      \
     template hipError_t launch_observe<S, R>(const void*, const void*, const Geo&,               \
                                              const Phys<R>&, int, void*, void*, void*, void*,    \
                                              double*, double*, hipStream_t);                     \
