@@ -43,7 +43,8 @@ TRAFFIC_PROFILES = {
     "step_kernel<float,float,true>": os.path.join(ROOT, "profiles",
                                                   "step_kernel_fp32_4096_traffic.md"),
 }
-STEP_SOURCES = ("paper_1308_2071_amd/csrc/lbm_device.hpp", "paper_1308_2071_amd/csrc/lbm_tile.hip",
+STEP_SOURCES = ("paper_1308_2071_amd/csrc/lbm_device.hpp", "paper_1308_2071_amd/csrc/lbm_tile.hpp",
+                "paper_1308_2071_amd/csrc/lbm_tile.hip",
                 "paper_1308_2071_amd/csrc/lbm_kernels.hip",
                 "paper_1308_2071_amd/csrc/lbm_internal.hpp",
                 "paper_1308_2071_amd/build.py")

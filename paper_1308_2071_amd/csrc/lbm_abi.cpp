@@ -330,9 +330,9 @@ struct lbm_ctx {
     size_t b_state_bytes = 0, b_off_buf[2] = {0, 0}, b_off_cav = 0, b_off_phys = 0;
     size_t b_off_tiles = 0, b_off_part = 0, b_max_tiles = 0;
     int b_wg = 4, b_npt = 1, b_nwg = 0, b_ntiles = 0;   // b_wg: rows per tile
-    // two steps per launch: rows per segment (0: one step per launch) and work-groups
+    // two steps per launch: rows per tile (0: one step per launch), tiles to 64 columns, tiles
     size_t b_off_cav2 = 0, b_off_tbwg = 0, b_max_tbwg = 0;
-    int b_tb_rows = 0, b_tb_nwg = 0, b_tb_waves = 4;
+    int b_tb_rows = 0, b_tb_nwg = 0, b_tb_per64 = 4;
 
     void* buf(int i) const { return ws + L.off_buf[i]; }
     void* medp() const { return med ? ws + L.off_med : nullptr; }
@@ -491,14 +491,11 @@ struct BatchLayout {
     size_t off_cav2, off_tbwg, max_tbwg;   // tables of the two-step form
 };
 
-// Work-groups of the batched two-step kernel for segments of `rows` rows, `waves` strips per
-// work-group.
-size_t batch_tb_groups(const std::vector<Geo>& G, int rows, int waves) {
+// Work-groups of the batched two-step kernel with tiles of `rows` rows, per64 to 64 columns.
+size_t batch_tb_groups(const std::vector<Geo>& G, int rows, int per64) {
+    const int cols = batch_tb_cols(per64);
     size_t n = 0;
-    for (const Geo& g : G) {
-        const size_t strips = size_t((g.nx + kTbCols - 1) / kTbCols);
-        n += (strips + waves - 1) / waves * size_t((g.ny + rows - 1) / rows);
-    }
+    for (const Geo& g : G) n += size_t((g.nx + cols - 1) / cols) * size_t((g.ny + rows - 1) / rows);
     return n;
 }
 
@@ -520,7 +517,7 @@ lbm_status batch_layout(int32_t n, const lbm_params* p, BatchLayout* L) {
                        p[0].steps_per_launch == kTinyTileSteps))
             return fail(LBM_E_UNSUPPORTED, "a batch steps one or two steps per launch");
         const Geo G = make_geo(p[i]);
-        if (p[0].steps_per_launch == 2 && tb2_descs(G, storage_bytes(dt)) != 1)
+        if (p[0].steps_per_launch == 2 && tb2_halves(G, storage_bytes(dt)) != 1)
             return fail(LBM_E_UNSUPPORTED,
                         "cavity %d: two steps per launch need a state below 2 GiB", i);
         L->off.push_back(elems);
@@ -550,7 +547,7 @@ lbm_status batch_layout(int32_t n, const lbm_params* p, BatchLayout* L) {
     L->off_cav2 = o;
     o += align_up(n * sizeof(BatchCavity));
     L->off_tbwg = o;
-    L->max_tbwg = batch_tb_groups(geos, kBatchTbMinRows, 1);  // the most: shortest rows, 1 strip
+    L->max_tbwg = batch_tb_groups(geos, kBatchTbMinRows, 4);  // the most: the smallest tiles
     o += align_up(L->max_tbwg * sizeof(int));
     L->off_part = o;
     o += align_up(size_t(n) * kBatchObsPer * sizeof(double));
@@ -610,22 +607,30 @@ BatchTable<R> batch_table(const lbm_ctx* c) {
     return T;
 }
 
-// Tables of the two-step form for segments of `rows` rows and `waves` strips per work-group:
-// per cavity its first logical work-group (tile0) and strip groups (tiles_x), and the
-// work-group -> cavity list.
-hipError_t batch_tb_tables(lbm_ctx* c, int rows, int waves) {
+// Tiles of the batched two-step kernel: rows, and how many of their regions make 64 columns.
+constexpr int kBatchTbRows[7] = {kBatchTbMinRows, 3, 4, 5, 6, 8, 12};
+constexpr int kBatchTbPer64[3] = {1, 2, 4};
+bool batch_tb_has(int rows, int per64) {
+    return std::count(kBatchTbRows, kBatchTbRows + 7, rows) > 0 &&
+           std::count(kBatchTbPer64, kBatchTbPer64 + 3, per64) > 0;
+}
+
+// Tables of the two-step form for tiles of `rows` rows, per64 to 64 columns: per cavity its first
+// tile (tile0) and tiles along x, and the tile -> cavity list.
+hipError_t batch_tb_tables(lbm_ctx* c, int rows, int per64) {
+    if (!batch_tb_has(rows, per64)) return hipErrorInvalidValue;
+    const int cols = batch_tb_cols(per64);
     std::vector<BatchCavity> cav(c->ncav);
     std::vector<int> wc;
     for (int i = 0; i < c->ncav; ++i) {
         const Geo& G = c->bG[i];
-        const int ngrp = ((G.nx + kTbCols - 1) / kTbCols + waves - 1) / waves;
         cav[i].G = G;
         cav[i].off = c->boff[i];
         cav[i].tile0 = int(wc.size());
-        cav[i].tiles_x = ngrp;
-        wc.insert(wc.end(), size_t(ngrp) * size_t((G.ny + rows - 1) / rows), i);
+        cav[i].tiles_x = (G.nx + cols - 1) / cols;
+        wc.insert(wc.end(), size_t(cav[i].tiles_x) * size_t((G.ny + rows - 1) / rows), i);
     }
-    if (rows < kBatchTbMinRows || wc.size() > c->b_max_tbwg) return hipErrorInvalidValue;
+    if (wc.size() > c->b_max_tbwg) return hipErrorInvalidValue;
     c->b_tb_nwg = int(wc.size());
     hipError_t e = hipMemcpy(c->ws + c->b_off_cav2, cav.data(), cav.size() * sizeof(BatchCavity),
                              hipMemcpyHostToDevice);
@@ -652,7 +657,7 @@ hipError_t batch_step2(lbm_ctx* c, int from, hipStream_t s) {
     return with_types(c->p.dtype, [&](auto st, auto rt) {
         LBM_TYPES(st, rt)
         return launch_batch_tb2<S, R>(src, dst, batch_tb_table<R>(c), c->b_tb_rows,
-                                      c->b_tb_waves, s);
+                                      c->b_tb_per64, s);
     });
 }
 
@@ -729,10 +734,10 @@ std::string batch_key(const lbm_ctx* c) {
 }
 
 // A cache line: key, rows per tile, 64-node segments per work-item, work-groups (0: one tile
-// per work-group), rows per segment of the two-step form (0: one step per launch) and its
-// strips per work-group.
+// per work-group), rows per tile of the two-step form (0: one step per launch) and how many of
+// its tiles' regions make 64 columns.
 bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, int* nwg,
-                  int* tb_rows, int* tb_waves) {
+                  int* tb_rows, int* tb_per64) {
     FILE* f = std::fopen(path, "r");
     if (!f) return false;
     char line[512], k[256];
@@ -744,7 +749,7 @@ bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, i
             *npt = b;
             *nwg = d;
             *tb_rows = t;
-            *tb_waves = w;
+            *tb_per64 = w;
             found = true;
         }
     std::fclose(f);
@@ -752,10 +757,10 @@ bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, i
 }
 
 void cache_store(const char* path, const std::string& key, int wg, int npt, int nwg,
-                 int tb_rows, int tb_waves) {
+                 int tb_rows, int tb_per64) {
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "%s %d %d %d %d %d\n", key.c_str(), wg, npt, nwg, tb_rows, tb_waves);
+    std::fprintf(f, "%s %d %d %d %d %d\n", key.c_str(), wg, npt, nwg, tb_rows, tb_per64);
     std::fclose(f);
 }
 
@@ -778,13 +783,14 @@ hipError_t time_steps(lbm_ctx* c, hipEvent_t e0, hipEvent_t e1, int steps_per_la
 
 // Autotuner, on the batch itself.  The one-step kernel: every supported tile shape (rows per
 // work-group x 64-node segments per work-item), with one tile per work-group and with chunked
-// persistent grids of 2..16 work-groups per CU.  The two-step kernel: segments of 2, 3, 4, 5,
-// 6, 8 and 12 rows with 1, 2 or 4 strips per work-group (short segments keep the launch's
-// tail short; on the 64-cavity workload 3 rows and one strip won, 61.4k against 60.3k MLUPS
-// for the best of 6 rows and up).  It keeps the fastest per step (the
-// one-step shape is kept either way, for odd step counts), unless steps_per_launch of the
-// first cavity forces one or two steps per launch.  The result is cached per (device, dtype,
-// cavity shapes, that setting) in tune_cache_path.
+// persistent grids of 2..16 work-groups per CU.  The two-step kernel: tiles of 2, 3, 4, 5, 6, 8
+// and 12 rows and 62, 30 or 14 columns.  It keeps the fastest per step (the one-step shape is
+// kept either way, for odd step counts), unless steps_per_launch of the first cavity forces one
+// or two steps per launch.  The result is cached per (device, dtype, cavity shapes, that setting)
+// in tune_cache_path.  Without a path, unless one step is asked for: two steps per launch in tiles
+// of 30 x 6 nodes, within 7 % of the best tile on batches of 300,000 to 5 million nodes (us per
+// step, FP32 / FP64: the 64-cavity workload 73.8 / 135 against 72.5 / 126, 8 cavities of 64^2 to
+// 250^2 5.7 / 8.8, the best; one step per launch took 102 / 213 and 11.1 / 20.1).
 lbm_status batch_tune(lbm_ctx* c, const char* path) {
     int cu = 256;
     int dev = 0;
@@ -795,7 +801,8 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
     int rows, npt, nwg, tbr, tbw;
     c->b_tb_rows = 0;
     c->b_tb_nwg = 0;
-    if (path && cache_lookup(path, key, &rows, &npt, &nwg, &tbr, &tbw)) {
+    if (path && cache_lookup(path, key, &rows, &npt, &nwg, &tbr, &tbw) &&
+        (tbr == 0 || batch_tb_has(tbr, tbw))) {
         c->b_wg = rows;
         c->b_npt = npt;
         HIP_TRY(batch_tables(c, 64 * npt, rows), "tile tables");
@@ -803,7 +810,7 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
         if (tbr > 0) {
             HIP_TRY(batch_tb_tables(c, tbr, tbw), "two-step tables");
             c->b_tb_rows = tbr;
-            c->b_tb_waves = tbw;
+            c->b_tb_per64 = tbw;
         }
         return LBM_OK;
     }
@@ -812,18 +819,16 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
         c->b_npt = 1;
         HIP_TRY(batch_tables(c, 64, 4), "tile tables");
         c->b_nwg = c->b_ntiles;
-        if (spl == 2) {
-            HIP_TRY(batch_tb_tables(c, 12, 4), "two-step tables");
-            c->b_tb_rows = 12;
-            c->b_tb_waves = 4;
+        if (spl != 1) {
+            HIP_TRY(batch_tb_tables(c, 6, 2), "two-step tables");
+            c->b_tb_rows = 6;
+            c->b_tb_per64 = 2;
         }
         return LBM_OK;
     }
     const int shapes[10][2] = {{1, 1}, {1, 2}, {1, 4}, {2, 1}, {2, 2}, {2, 4},
                                {4, 1}, {4, 2}, {4, 4}, {8, 1}};
     const int per_cu[5] = {0, 2, 4, 8, 16};  // 0: one tile per work-group
-    const int tb_rows[7] = {kBatchTbMinRows, 3, 4, 5, 6, 8, 12};
-    const int tb_waves[3] = {1, 2, 4};
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0), "event");
     HIP_TRY(hipEventCreate(&e1), "event");
@@ -850,16 +855,13 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
         }
         if (st != LBM_OK) break;
     }
-    bool fit = true;  // the two-step kernel needs each cavity's state below 2 GiB
-    for (int i = 0; i < c->ncav; ++i)
-        fit = fit && tb2_descs(c->bG[i], storage_bytes(c->p.dtype)) == 1;
-    if (st == LBM_OK && spl != 1 && fit) {
-        for (int tr : tb_rows) {
-            for (int tw : tb_waves) {
+    if (st == LBM_OK && spl != 1) {
+        for (int tr : kBatchTbRows) {
+            for (int tw : kBatchTbPer64) {
                 hipError_t e = batch_tb_tables(c, tr, tw);
                 if (e != hipSuccess) { st = hip_fail(e, "two-step tables"); break; }
                 c->b_tb_rows = tr;
-                c->b_tb_waves = tw;
+                c->b_tb_per64 = tw;
                 float ms = 0;
                 e = time_steps(c, e0, e1, 2,
                                [&](int from) { return batch_step2(c, from, c->stream); }, &ms);
@@ -886,7 +888,7 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
     if (use_tr > 0) {
         HIP_TRY(batch_tb_tables(c, use_tr, btw), "two-step tables");
         c->b_tb_rows = use_tr;
-        c->b_tb_waves = btw;
+        c->b_tb_per64 = btw;
     }
     cache_store(path, key, br, bn, bg, use_tr, btw);
     return LBM_OK;
@@ -1385,11 +1387,6 @@ lbm_status lbm_batch_init(lbm_ctx** out, int32_t n, const lbm_params* p,
         delete c;
         return hip_fail(e, "lbm_batch_init");
     }
-    with_types(p[0].dtype, [&](auto st, auto rt) {
-        LBM_TYPES(st, rt)
-        prepare_batch_tb2<S, R>();
-        return 0;
-    });
     s = batch_tune(c, tune_cache_path);
     if (s == LBM_OK) {
         hipError_t e2 = batch_rest(c);  // tuning stepped the cavities: back to rest
@@ -1514,7 +1511,7 @@ lbm_status lbm_batch_shape(const lbm_ctx* c, int32_t* out) {
     out[4] = c->b_tb_rows > 0 ? 2 : 1;
     out[5] = c->b_tb_rows;
     out[6] = c->b_tb_nwg;
-    out[7] = c->b_tb_rows > 0 ? c->b_tb_waves : 0;
+    out[7] = c->b_tb_rows > 0 ? c->b_tb_per64 : 0;
     return LBM_OK;
 }
 

@@ -8,7 +8,7 @@
 // result is bitwise that of its own plain run.
 #include "lbm_device.hpp"
 #include "lbm_internal.hpp"
-#include "lbm_tb2.hpp"
+#include "lbm_tile.hpp"
 
 namespace lbm {
 
@@ -99,72 +99,57 @@ hipError_t launch_batch_step(const void* src, void* dst, const BatchTable<R>& T,
     }
 }
 
-// Two steps per launch for every cavity (the single-cavity two-step kernel's work, uniform
-// medium per cavity), TW strips (wavefronts) per work-group: narrow cavities leave fewer
-// wavefronts idle with fewer strips per group.  The logical work-groups of all cavities form
-// one list: wg_cav[w] is the cavity of logical work-group w, and for that cavity C.tile0 is its
-// first logical work-group and C.tiles_x its number of strip groups.
-template <typename S, typename R, int TW>
-__global__ __launch_bounds__(64 * TW, (tb_min_waves<S, R>())) void batch_tb2_kernel(
+// Two steps per launch for every cavity: tiles of TX x TY nodes in LDS as in the single cavity's
+// kernel, uniform medium per cavity.  The tiles of all cavities form one list, of which each XCD
+// takes a contiguous run: wg_cav[t] is the cavity of tile t, C.tile0 its first tile and C.tiles_x
+// its tiles along x.
+template <typename S, typename R, int TX, int TY, int NT>
+__global__ __launch_bounds__(NT, (sizeof(R) == 4 ? 6 : 4)) void batch_tb2_kernel(
     const S* __restrict__ src, S* __restrict__ dst, const BatchCavity* __restrict__ cav,
-    const Phys<R>* __restrict__ phys, const int* __restrict__ wg_cav, int rows, int chunk) {
-    const int wg = tb_logical_group(chunk);
-    const int c = wg_cav[wg];
+    const Phys<R>* __restrict__ phys, const int* __restrict__ wg_cav) {
+    const int t = tile_index();
+    const int c = wg_cav[t];
     const BatchCavity C = cav[c];
     const Phys<R> P = phys[c];
-    const int lw = wg - C.tile0;
-    const int nstrips = (C.G.nx + kTbCols - 1) / kTbCols;
-    const int strip = (lw % C.tiles_x) * TW + (threadIdx.x >> 6), seg = lw / C.tiles_x;
-    tb2_segment<S, R, false>(src + C.off, dst + C.off, (const S*)nullptr, C.G, P, strip,
-                             strip < nstrips, seg, rows);
+    const int lt = t - C.tile0, ty = lt / C.tiles_x;
+    tile_steps_body<S, R, false, TX, TY, 2, NT>(src + C.off, dst + C.off, (const S*)nullptr, C.G,
+                                                P, lt - ty * C.tiles_x, ty);
 }
 
-// Work-groups of batch_tb2_kernel<S, R, TW> one XCD holds at once (the XCD chunk of
-// tb_logical_group); queried once, at the first call.
-template <typename S, typename R, int TW>
-static int batch_tb_chunk() {
-    static const int chunk = [] {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_tb2_kernel<S, R, TW>,
-                                                         64 * TW, 0) != hipSuccess)
-            return 1;
-        return max(1, cus * per_cu / 8);
-    }();
-    return chunk;
+template <typename S, typename R, int TX, int TY>
+static hipError_t launch_tb2_v(const void* src, void* dst, const BatchTable<R>& T,
+                               hipStream_t s) {
+    constexpr int NT = (TileRegion<TX, TY, 2>::N + 63) / 64 * 64;
+    constexpr size_t lds = tile_lds_bytes<S, R, false, TX, TY, 2>();
+    batch_tb2_kernel<S, R, TX, TY, NT><<<T.ntiles, NT, lds, s>>>((const S*)src, (S*)dst, T.cav,
+                                                                 T.phys, T.tile_cav);
+    return hipGetLastError();
 }
 
-template <typename S, typename R>
-void prepare_batch_tb2() {
-    (void)batch_tb_chunk<S, R, 1>();
-    (void)batch_tb_chunk<S, R, 2>();
-    (void)batch_tb_chunk<S, R, 4>();
+template <typename S, typename R, int TY>
+static hipError_t launch_tb2_rows(const void* src, void* dst, const BatchTable<R>& T, int per64,
+                                  hipStream_t s) {
+    switch (per64) {
+        case 1: return launch_tb2_v<S, R, batch_tb_cols(1), TY>(src, dst, T, s);
+        case 2: return launch_tb2_v<S, R, batch_tb_cols(2), TY>(src, dst, T, s);
+        case 4: return launch_tb2_v<S, R, batch_tb_cols(4), TY>(src, dst, T, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <typename S, typename R>
 hipError_t launch_batch_tb2(const void* src, void* dst, const BatchTable<R>& T, int rows,
-                            int waves, hipStream_t s) {
-    switch (waves) {
-        case 1:
-            batch_tb2_kernel<S, R, 1><<<T.ntiles, 64, 0, s>>>(
-                (const S*)src, (S*)dst, T.cav, T.phys, T.tile_cav, rows,
-                batch_tb_chunk<S, R, 1>());
-            break;
-        case 2:
-            batch_tb2_kernel<S, R, 2><<<T.ntiles, 128, 0, s>>>(
-                (const S*)src, (S*)dst, T.cav, T.phys, T.tile_cav, rows,
-                batch_tb_chunk<S, R, 2>());
-            break;
-        case 4:
-            batch_tb2_kernel<S, R, 4><<<T.ntiles, 256, 0, s>>>(
-                (const S*)src, (S*)dst, T.cav, T.phys, T.tile_cav, rows,
-                batch_tb_chunk<S, R, 4>());
-            break;
+                            int per64, hipStream_t s) {
+    switch (rows) {
+        case 2: return launch_tb2_rows<S, R, 2>(src, dst, T, per64, s);
+        case 3: return launch_tb2_rows<S, R, 3>(src, dst, T, per64, s);
+        case 4: return launch_tb2_rows<S, R, 4>(src, dst, T, per64, s);
+        case 5: return launch_tb2_rows<S, R, 5>(src, dst, T, per64, s);
+        case 6: return launch_tb2_rows<S, R, 6>(src, dst, T, per64, s);
+        case 8: return launch_tb2_rows<S, R, 8>(src, dst, T, per64, s);
+        case 12: return launch_tb2_rows<S, R, 12>(src, dst, T, per64, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template hipError_t launch_batch_step<float, float>(const void*, void*, const BatchTable<float>&,
@@ -175,9 +160,6 @@ template hipError_t launch_batch_step<double, double>(const void*, void*,
 template hipError_t launch_batch_step<float, double>(const void*, void*,
                                                      const BatchTable<double>&, int, int, int,
                                                      hipStream_t);
-template void prepare_batch_tb2<float, float>();
-template void prepare_batch_tb2<double, double>();
-template void prepare_batch_tb2<float, double>();
 template hipError_t launch_batch_tb2<float, float>(const void*, void*, const BatchTable<float>&,
                                                    int, int, hipStream_t);
 template hipError_t launch_batch_tb2<double, double>(const void*, void*,

@@ -25,17 +25,10 @@ constexpr int kPlanePad = 1056;
 // Elements per plane: ny rows of the pitch, then the pad.
 inline long long plane_elems(long long pitch, long long ny) { return pitch * ny + kPlanePad; }
 
-// Two steps per launch of the batch: columns a wavefront's strip writes.
-constexpr int kTbCols = 62;
-// The shortest segment the batch's autotuner tries.
+// Two steps per launch of the batch: columns of a tile whose region (one node more on each side)
+// is 64 / per64 columns wide, and the fewest rows of a tile.
+constexpr int batch_tb_cols(int per64) { return 64 / per64 - 2; }
 constexpr int kBatchTbMinRows = 2;
-// Minimum wavefronts per SIMD the two-step kernels are compiled for: in FP32 four, the
-// occupancy their ~128 registers allow (the compiler would otherwise settle for 129 registers
-// and three); the FP64-arithmetic forms take what their registers give.
-template <typename S, typename R>
-constexpr int tb_min_waves() {
-    return sizeof(S) == 4 && sizeof(R) == 4 ? 4 : 1;
-}
 
 // Tile side and steps per launch of the forms for small grids (lbm_tile.hip).
 constexpr int kTileSide = 16;
@@ -43,12 +36,9 @@ constexpr int kTileSteps = 4;
 constexpr int kTinyTileSide = 8;
 constexpr int kTinyTileSteps = 8;
 
-// The two-step kernels address a state (the 14 planes) through raw buffer descriptors and drop
-// stores through an offset of 2^31 past them, so a descriptor covers less than 2^31 bytes: one
-// descriptor for a state below 2^31 bytes, two (planes 0-6 and 7-13) for a state whose halves
-// are.  tb2_descs gives the number of descriptors a state needs, 0 if even its halves are too
-// large.  The batched two-step kernel uses one descriptor per cavity.
-inline int tb2_descs(const Geo& G, size_t elem_bytes) {
+// What steps_per_launch = 2 asks of a state: 1 where its 14 planes, 2 where only each half of them
+// (7 planes) is below 2 GiB, 0 beyond.
+inline int tb2_halves(const Geo& G, size_t elem_bytes) {
     const unsigned long long pb = (unsigned long long)G.plane * elem_bytes;
     if (kPlanes * pb < (1ull << 31)) return 1;
     if (kPlanes / 2 * pb < (1ull << 31)) return 2;
@@ -122,15 +112,12 @@ struct BatchTable {
     int ntiles;
 };
 
-// Two steps per launch for every cavity of a batch: T.tile_cav maps each logical work-group to
-// its cavity, whose tile0 is its first work-group and tiles_x its number of strip groups (of
-// `waves` strips: 1, 2 or 4); rows: rows per segment.
+// Two steps per launch for every cavity of a batch, in tiles of `rows` rows (2, 3, 4, 5, 6, 8 or
+// 12) and batch_tb_cols(per64) columns (per64 1, 2 or 4): T.tile_cav maps each of the T.ntiles
+// tiles to its cavity, whose tile0 is its first tile and tiles_x its tiles along x.
 template <typename S, typename R>
 hipError_t launch_batch_tb2(const void* src, void* dst, const BatchTable<R>& T, int rows,
-                            int waves, hipStream_t s);
-// Queries the batched two-step kernel's resident set once (call outside graph capture)
-template <typename S, typename R>
-void prepare_batch_tb2();
+                            int per64, hipStream_t s);
 
 // Observables of every cavity (no fields): results of cavity i at out[kObsOut * i]; part has room
 // for kObsParts * kBatchObsWG + 2 * kNuWG doubles per cavity; largest: nodes of the largest one.
