@@ -1249,15 +1249,35 @@ lbm_status lbm_grad(lbm_ctx* c, double dJ, void* dJ_dphi, void* dJ_dK) {
                            }),
                 "adjoint seed");
         const int64_t nseg = (N + C - 1) / C;
-        // X^{n0} .. X^{n0+len-1} of segment sg, recomputed from its checkpoint into bank sg % 2
+        // X^{n0} of segment sg is its checkpoint; X^{n0+1} .. X^{n0+len-1} are recomputed into
+        // bank sg % 2, as many steps per launch as the grid takes by default.
+        const int most = with_types(c->p.dtype, [&](auto stt, auto rt) {
+            LBM_TYPES(stt, rt)
+            return default_steps<S, R>(c->G, c->med);
+        });
+        const bool by_tiles = with_types(c->p.dtype, [&](auto stt, auto rt) {
+            LBM_TYPES(stt, rt)
+            return adjoint_by_tiles<S, R>(c->G);
+        });
+        auto state = [&](int64_t sg, int64_t k) -> void* {
+            return k == 0 ? c->ckpt(size_t(sg)) : c->seg(int(sg & 1), size_t(k));
+        };
         auto recompute = [&](int64_t sg) -> hipError_t {
-            const int bank = int(sg & 1);
             const int64_t len = std::min<int64_t>(C, N - sg * C);
-            hipError_t e = hipMemcpyAsync(c->seg(bank, 0), c->ckpt(size_t(sg)),
-                                          c->L.state_bytes, hipMemcpyDeviceToDevice, aux);
-            for (int64_t k = 1; k < len && e == hipSuccess; ++k)
-                e = step_once(c, c->seg(bank, size_t(k - 1)), c->seg(bank, size_t(k)), aux);
-            if (e == hipSuccess) e = hipEventRecord(c->ev_rec[bank], aux);
+            hipError_t e = hipSuccess;
+            for (int64_t k = 0; k < len - 1 && e == hipSuccess;) {
+                const int64_t left = len - 1 - k;
+                const int m = left >= most ? most : left >= 2 ? 2 : 1;
+                e = m == 1 ? step_once(c, state(sg, k), state(sg, k + 1), aux)
+                           : with_types(c->p.dtype, [&](auto stt, auto rt) {
+                                 LBM_TYPES(stt, rt)
+                                 return launch_tile_trace<S, R>(state(sg, k), state(sg, k + 1),
+                                                                nel, c->medp(), c->G, phys<R>(c),
+                                                                m, aux);
+                             });
+                k += m;
+            }
+            if (e == hipSuccess) e = hipEventRecord(c->ev_rec[int(sg & 1)], aux);
             return e;
         };
         // The backward sweep of segment sg (on the caller's stream) overlaps the recompute of
@@ -1275,17 +1295,26 @@ lbm_status lbm_grad(lbm_ctx* c, double dJ, void* dJ_dphi, void* dJ_dK) {
                     HIP_TRY(recompute(sg - 1), "recompute launch");
                 }
                 HIP_TRY(hipStreamWaitEvent(st, c->ev_rec[bank], 0), "stream wait");
-                for (int64_t k = len - 1; k >= 0; --k) {
-                    const void* X = c->seg(bank, size_t(k));
+                for (int64_t k = len - 1; k >= 0;) {
+                    const bool tiles = by_tiles && k + 1 >= kAdjSteps;
+                    const int m = tiles ? kAdjSteps : 1;
+                    const void* X[kAdjSteps] = {};
+                    for (int j = 0; j < m; ++j) X[j] = state(sg, k - j);
                     HIP_TRY(with_types(c->p.dtype,
                                        [&](auto stt, auto rt) {
                                            LBM_TYPES(stt, rt)
-                                           return launch_adjoint_step<S, R>(
-                                               X, c->lam(lc), c->lam(1 - lc), c->medp(), gphi,
-                                               gK, c->G, phys<R>(c), st);
+                                           return tiles ? launch_adjoint_tiles<S, R>(
+                                                              X, c->lam(lc), c->lam(1 - lc),
+                                                              c->medp(), gphi, gK, c->G,
+                                                              phys<R>(c), st)
+                                                        : launch_adjoint_step<S, R>(
+                                                              X[0], c->lam(lc), c->lam(1 - lc),
+                                                              c->medp(), gphi, gK, c->G,
+                                                              phys<R>(c), st);
                                        }),
                             "adjoint step launch");
                     lc = 1 - lc;
+                    k -= m;
                 }
                 HIP_TRY(hipEventRecord(c->ev_bwd[bank], st), "event");
             }

@@ -119,7 +119,7 @@ __device__ __forceinline__ void macros_vjp(const R f[9], const R g[5], R phi, R 
     const Vel<R> v = velocity<R>(f, g, md, P);
     const R Gx = v.Gx, Gy = v.Gy, hphi = R(0.5) * phi;
     const R vx = v.vx, vy = v.vy, l0 = v.l0, l1 = v.l1, vm = v.vm, q = v.q;
-    const R inv_den = R(1) / v.den;
+    const R inv_den = reciprocal(v.den), rq = recip(q), rK = recip(K);
     const R ux = v.ux, uy = v.uy, uu = v.uu, um = v.um, drag = v.drag;
     // reverse
     R lux = A0.ux, luy = A0.uy, lth = A0.theta, lip = A0.ip;
@@ -144,9 +144,9 @@ __device__ __forceinline__ void macros_vjp(const R f[9], const R g[5], R phi, R 
     R lvx = lux * inv_den, lvy = luy * inv_den;
     const R lden = -(lux * ux + luy * uy) * inv_den;
     const R lq = lden;
-    const R ll0 = lden + lq * l0 / q;
-    const R ll1 = lq * vm / (R(2) * q);
-    const R lvm = lq * l1 / (R(2) * q);
+    const R ll0 = lden + quotient(lq * l0, q, rq);
+    const R ll1 = quotient(lq * vm, R(2) * q, R(0.5) * rq);
+    const R lvm = quotient(lq * l1, R(2) * q, R(0.5) * rq);
     if (vm > R(0)) {                  // d|v|/dv, taken as 0 at v = 0
         lvx += lvm * vx / vm;
         lvy += lvm * vy / vm;
@@ -163,9 +163,9 @@ __device__ __forceinline__ void macros_vjp(const R f[9], const R g[5], R phi, R 
     // medium: ip = 1/phi, c_lin = phi nu / K, c_nl = C phi^(-1/2) K^(-1/2)
     lphi += -md.inv_phi * md.inv_phi * lip;
     lphi += md.c_lin * md.inv_phi * lclin;
-    lK += -md.c_lin / K * lclin;
+    lK += quotient(-md.c_lin, K, rK) * lclin;
     lphi += R(-0.5) * md.c_nl * md.inv_phi * lcnl;
-    lK += R(-0.5) * md.c_nl / K * lcnl;
+    lK += quotient(R(-0.5) * md.c_nl, K, rK) * lcnl;
     // populations
     af[1] += ljx + lsum18;
     af[2] += ljy + lsum18;
@@ -244,128 +244,123 @@ __device__ __forceinline__ void adj_span(int t, int T, int side, int last0, int 
     b = t == T - 1 ? n : min((t + 1) * side, last0);
 }
 
-// One backward step.  state: the forward state X^n (post-collision populations entering step
-// n); lam_in: adjoint of X^{n+1}; lam_out: adjoint of X^n (written); gphi, gK: FP64 gradient
-// planes [ny][pitch] accumulated in place.  S: storage type of state, adjoint and medium;
-// R: arithmetic type.
-//
-// A fluid node's work-item reverses its own collision and macroscopics.  A wall node's
-// work-item runs the same gather, macroscopics and collision VJP on the wall node's own
-// reconstructed state (so both kinds of node stay in step), adds its dJ/dphi (through
-// F_b = phi_b G_b), writes zeros to its own slots (the forward step never reads them) and hands
-// its inward neighbour, through LDS, what flows back through the reconstruction.  After one
-// barrier the neighbour adds up to three hand-offs (two sides and their corner) in a fixed
-// order before reversing its own macroscopics.
-template <typename S, typename R, bool PN>
-__global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
-    const S* __restrict__ state, const S* __restrict__ lam_in, S* __restrict__ lam_out,
-    const S* __restrict__ med, double* __restrict__ gphi, double* __restrict__ gK, Geo G,
-    Phys<R> P, AdjTiles T) {
-    __shared__ R handoff[kHandoff][kAdjThreads];
-    const int tx = blockIdx.x % T.nx_tiles, ty = blockIdx.x / T.nx_tiles;
-    int x0, x1, y0, y1;
-    adj_span(tx, T.nx_tiles, kAdjTX, T.last_x0, G.nx, x0, x1);
-    adj_span(ty, T.ny_tiles, kAdjTY, T.last_y0, G.ny, y0, y1);
-    const int me = threadIdx.x;
-    const int x = x0 + me % kAdjTX, y = y0 + me / kAdjTX;
-    const bool active = x < x1 && y < y1;
-    const bool onW = G.wallW && x == 0, onE = G.wallE && x == G.nx - 1;
-    const bool onS = G.wallS && y == 0, onN = G.wallN && y == G.ny - 1;
-    const bool wall = onW || onE || onS || onN;
-    const int o = y * G.pitch + x;
-    const int xm = (x == 0) ? G.nx - 1 : x - 1;
-    const int xp = (x == G.nx - 1) ? 0 : x + 1;
-    const int ym = (y == 0) ? G.ny - 1 : y - 1;
-    const int yp = (y == G.ny - 1) ? 0 : y + 1;
-    // slot owned by this node for population i: (i, x - e_i); valid unless it leaves a walled
-    // side of the domain
-    const int sx[9] = {x, xm, x, xp, x, xm, xp, xp, xm};
-    const int sy[9] = {y, y, ym, y, yp, ym, ym, yp, yp};
+// A node's backward step up to the point where wall nodes hand their share over, and from there.
+template <typename R>
+struct AdjNode {
+    R f[9], g[5], af[9], ag[5], phi, K;
+    Med<R> md;
+    MacAdj<R> A;
+    MacAdj<R> H;    // wall node: what its inward neighbour's macroscopics receive
+    R lphib;        // wall node: its dJ/dphi
+};
 
-    R f[9], g[5], af[9], ag[5], phi = 0, K = 0;
-    Med<R> md{};
-    MacAdj<R> A{};
-    // the gradient planes are read before the barrier, which global loads do not cross, so
-    // that their latency hides behind the step's arithmetic
-    double gphi0 = 0, gK0 = 0;
-    if (active) {
-        gphi0 = gphi[o];
-        if (!wall) gK0 = gK[o];
-        // the node whose pulled populations this node's state is built from: itself, or its
-        // inward neighbour (the diagonal one at a corner)
-        const int px = x + (onW ? 1 : 0) - (onE ? 1 : 0);
-        const int py = y + (onS ? 1 : 0) - (onN ? 1 : 0);
-        pull<R, S>(state, G, px, py, f, g);
-        if constexpr (PN) {
-            const int op = py * G.pitch + px;
-            phi = R(med[op]);
-            K = R(med[G.plane + op]);
-            md = medium_from<R>(phi, K, P);
-        } else {
-            phi = P.phi;
-            K = P.c_lin > R(0) ? phi * P.nu / P.c_lin : R(INFINITY);
-            md = Med<R>{P.phi, P.inv_phi, P.c_lin, P.c_nl};
-        }
-        const Mac<R> m = fluid_macros<R>(f, g, md, P);
-        R lout[14];
+// Byte offsets, within a plane, of the node (x, y) and of the slots it owns: o[i] that of slot
+// (i, x - e_i), wrapped (a slot beyond a wall is never used).  32-bit offsets from a plane's
+// uniform base, as in pull: one vector register per place and no 64-bit arithmetic per access.
+template <typename S>
+struct AdjSlots {
+    unsigned o[9];
+    __device__ __forceinline__ AdjSlots(const Geo& G, int x, int y) {
+        constexpr unsigned B = sizeof(S);
+        const unsigned x0 = unsigned(x), xm = unsigned(x == 0 ? G.nx - 1 : x - 1);
+        const unsigned xp = unsigned(x == G.nx - 1 ? 0 : x + 1);
+        const unsigned pitch = unsigned(G.pitch), r0 = unsigned(y) * pitch;
+        const unsigned rm = unsigned(y == 0 ? G.ny - 1 : y - 1) * pitch;
+        const unsigned rp = unsigned(y == G.ny - 1 ? 0 : y + 1) * pitch;
+        const unsigned q[9] = {r0 + x0, r0 + xm, rm + x0, r0 + xp, rp + x0,
+                               rm + xm, rm + xp, rp + xp, rp + xm};
 #pragma unroll
-        for (int i = 0; i < 14; ++i) lout[i] = R(lam_in[i * G.plane + o]);
-        Mac<R> mc = m;
-        Med<R> mdc = md;
-        R theta_b = 0, phi_b = 0;
-        if (wall) {
-            // the wall node's state: rebuilt from its neighbour's, at rest, with its own phi
-            theta_b = wall_theta<R>(onW, onE, onS, onN, m.theta, P);
-            nee_wall<R>(f, g, m, md, theta_b, P);
-            phi_b = PN ? R(med[o]) : P.phi;
-            mc.theta = theta_b;
-            mc.ux = R(0);
-            mc.uy = R(0);
-            mc.Fx = phi_b * P.ax;
-            mc.Fy = phi_b * (P.ay + P.gbeta * theta_b);
-            mdc = Med<R>{phi_b, R(1) / phi_b, R(0), R(0)};
-        }
-#pragma unroll
-        for (int i = 0; i < 9; ++i) af[i] = R(0);
-#pragma unroll
-        for (int i = 0; i < 5; ++i) ag[i] = R(0);
-        collide_vjp<R>(f, g, mc, mdc, P, lout, lout + 9, af, ag, A);
-        if (wall) {
-            // at rest the collision depends on 1/phi_b only through terms in u = 0, so phi_b
-            // acts through F_b alone; theta_b through the collision, F_b and the rebuilt g
-            const R Gy = P.ay + P.gbeta * theta_b;
-            const R lphib = P.ax * A.Fx + Gy * A.Fy;
-            const R lthb = A.theta + phi_b * P.gbeta * A.Fy;
-            MacAdj<R> H{};
-            const R sw = nee_vjp<R>(m, md, P, af, ag, H);
-            const bool adiabatic = !((onW && P.iso[0]) || (onE && P.iso[1]) ||
-                                     (onS && P.iso[2]) || (onN && P.iso[3]));
-            if (adiabatic) H.theta += lthb + sw;    // theta_b = theta_f on an adiabatic side
-#pragma unroll
-            for (int i = 0; i < 9; ++i) handoff[i][me] = af[i];
-#pragma unroll
-            for (int i = 0; i < 5; ++i) handoff[9 + i][me] = ag[i];
-            handoff[14][me] = H.ux;
-            handoff[15][me] = H.uy;
-            handoff[16][me] = H.ip;
-            handoff[17][me] = H.theta;
-            handoff[18][me] = A.P;
-            const bool okx_m = !onW, okx_p = !onE, oky_m = !onS, oky_p = !onN;
-            const bool ok[9] = {true, okx_m, oky_m, okx_p, oky_p, okx_m && oky_m,
-                                okx_p && oky_m, okx_p && oky_p, okx_m && oky_p};
-#pragma unroll
-            for (int i = 0; i < 9; ++i)
-                if (ok[i]) lam_out[i * G.plane + sy[i] * G.pitch + sx[i]] = S(0);
-#pragma unroll
-            for (int i = 0; i < 5; ++i)
-                if (ok[i]) lam_out[(9 + i) * G.plane + sy[i] * G.pitch + sx[i]] = S(0);
-            gphi[o] = gphi0 + double(lphib);
-        }
+        for (int i = 0; i < 9; ++i) o[i] = q[i] * B;
     }
-    __syncthreads();
-    if (!active || wall) return;
+};
 
-    // hand-offs of the wall nodes whose inward neighbour this node is, in a fixed order
+// Slots a node owns (population i at x - e_i), relative to the node.
+__device__ constexpr int kEx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
+__device__ constexpr int kEy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
+
+// state: the forward state X^n (post-collision populations entering step n); lout: adjoint of
+// X^{n+1} in the node's own 14 slots; (x, y) in the grid.  A fluid node reverses its own
+// collision.  A wall node runs the same gather, macroscopics and collision VJP on its own
+// reconstructed state (so both kinds of node stay in step), then reverses the reconstruction.
+template <typename S, typename R, bool PN>
+__device__ __forceinline__ void adj_open(const S* __restrict__ state, const S* __restrict__ med,
+                                         const Geo& G, const Phys<R>& P, int x, int y, bool onW,
+                                         bool onE, bool onS, bool onN, const R lout[14],
+                                         AdjNode<R>& w) {
+    const bool wall = onW || onE || onS || onN;
+    // the node whose pulled populations this node's state is built from: itself, or its inward
+    // neighbour (the diagonal one at a corner)
+    const int px = x + (onW ? 1 : 0) - (onE ? 1 : 0);
+    const int py = y + (onS ? 1 : 0) - (onN ? 1 : 0);
+    R (&f)[9] = w.f;
+    R (&g)[5] = w.g;
+    pull<R, S>(state, G, px, py, f, g);
+    if constexpr (PN) {
+        const unsigned op = (unsigned(py) * unsigned(G.pitch) + unsigned(px)) * unsigned(sizeof(S));
+        w.phi = R(at(med, op));
+        w.K = R(at(plane(med, 1, G.plane), op));
+        w.md = medium_from<R>(w.phi, w.K, P);
+    } else {
+        w.phi = P.phi;
+        w.K = P.c_lin > R(0) ? w.phi * P.nu / P.c_lin : R(INFINITY);
+        w.md = Med<R>{P.phi, P.inv_phi, P.c_lin, P.c_nl};
+    }
+    const Mac<R> m = fluid_macros<R>(f, g, w.md, P);
+    Mac<R> mc = m;
+    Med<R> mdc = w.md;
+    R theta_b = 0, phi_b = 0;
+    if (wall) {
+        // the wall node's state: rebuilt from its neighbour's, at rest, with its own phi
+        theta_b = wall_theta<R>(onW, onE, onS, onN, m.theta, P);
+        nee_wall<R>(f, g, m, w.md, theta_b, P);
+        phi_b = PN ? R(med[size_t(y) * G.pitch + x]) : P.phi;
+        mc.theta = theta_b;
+        mc.ux = R(0);
+        mc.uy = R(0);
+        mc.Fx = phi_b * P.ax;
+        mc.Fy = phi_b * (P.ay + P.gbeta * theta_b);
+        mdc = Med<R>{phi_b, reciprocal(phi_b), R(0), R(0)};
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) w.af[i] = R(0);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) w.ag[i] = R(0);
+    w.A = MacAdj<R>{};
+    collide_vjp<R>(f, g, mc, mdc, P, lout, lout + 9, w.af, w.ag, w.A);
+    if (wall) {
+        // at rest the collision depends on 1/phi_b only through terms in u = 0, so phi_b
+        // acts through F_b alone; theta_b through the collision, F_b and the rebuilt g
+        const R Gy = P.ay + P.gbeta * theta_b;
+        w.lphib = P.ax * w.A.Fx + Gy * w.A.Fy;
+        const R lthb = w.A.theta + phi_b * P.gbeta * w.A.Fy;
+        w.H = MacAdj<R>{};
+        const R sw = nee_vjp<R>(m, w.md, P, w.af, w.ag, w.H);
+        const bool adiabatic = !((onW && P.iso[0]) || (onE && P.iso[1]) || (onS && P.iso[2]) ||
+                                 (onN && P.iso[3]));
+        if (adiabatic) w.H.theta += lthb + sw;    // theta_b = theta_f on an adiabatic side
+    }
+}
+
+// Value i of the kHandoff values a wall node hands over.
+template <typename R, typename Put>
+__device__ __forceinline__ void adj_hand_over(const AdjNode<R>& w, Put&& put) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) put(i, w.af[i]);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) put(9 + i, w.ag[i]);
+    put(14, w.H.ux);
+    put(15, w.H.uy);
+    put(16, w.H.ip);
+    put(17, w.H.theta);
+    put(18, w.A.P);
+}
+
+// A fluid node at (x, y) takes the hand-offs of the wall nodes whose inward neighbour it is, in a
+// fixed order (get(i, dx, dy): value i of the wall node at (x + dx, y + dy)), then reverses its
+// own macroscopics; af, ag become the adjoint of the slots it owns.
+template <typename R, typename Get>
+__device__ __forceinline__ void adj_close(const Geo& G, const Phys<R>& P, int x, int y,
+                                          AdjNode<R>& w, R& lphi, R& lK, Get&& get) {
     const bool nearW = G.wallW && x == 1, nearE = G.wallE && x == G.nx - 2;
     const bool nearS = G.wallS && y == 1, nearN = G.wallN && y == G.ny - 2;
     if (nearW || nearE || nearS || nearN) {
@@ -376,26 +371,231 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             if (!has[k]) continue;
-            const int j = me + dys[k] * kAdjTX + dxs[k];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) af[i] += handoff[i][j];
+            for (int i = 0; i < 9; ++i) w.af[i] += get(i, dxs[k], dys[k]);
 #pragma unroll
-            for (int i = 0; i < 5; ++i) ag[i] += handoff[9 + i][j];
-            A.ux += handoff[14][j];
-            A.uy += handoff[15][j];
-            A.ip += handoff[16][j];
-            A.theta += handoff[17][j];
-            A.P += handoff[18][j];
+            for (int i = 0; i < 5; ++i) w.ag[i] += get(9 + i, dxs[k], dys[k]);
+            w.A.ux += get(14, dxs[k], dys[k]);
+            w.A.uy += get(15, dxs[k], dys[k]);
+            w.A.ip += get(16, dxs[k], dys[k]);
+            w.A.theta += get(17, dxs[k], dys[k]);
+            w.A.P += get(18, dxs[k], dys[k]);
         }
     }
-    R lphi = 0, lK = 0;
-    macros_vjp<R>(f, g, phi, K, md, P, A, af, ag, lphi, lK);
+    lphi = R(0);
+    lK = R(0);
+    macros_vjp<R>(w.f, w.g, w.phi, w.K, w.md, P, w.A, w.af, w.ag, lphi, lK);
+}
+
+// One backward step.  state: X^n; lam_in: adjoint of X^{n+1}; lam_out: adjoint of X^n (written);
+// gphi, gK: FP64 gradient planes [ny][pitch] accumulated in place.  S: storage type of state,
+// adjoint and medium; R: arithmetic type.
+//
+// A wall node's work-item adds its dJ/dphi (through F_b = phi_b G_b), writes zeros to its own
+// slots (the forward step never reads them) and hands its inward neighbour, through LDS, what
+// flows back through the reconstruction.  After one barrier the neighbour adds up to three
+// hand-offs (two sides and their corner) before reversing its own macroscopics.
+template <typename S, typename R, bool PN>
+__global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
+    const S* __restrict__ state, const S* __restrict__ lam_in, S* __restrict__ lam_out,
+    const S* __restrict__ med, double* __restrict__ gphi, double* __restrict__ gK, Geo G,
+    Phys<R> P, AdjTiles T) {
+    __shared__ R handoff[kHandoff][kAdjThreads];
+    const int t = tile_index(), ty = t / T.nx_tiles, tx = t - ty * T.nx_tiles;
+    int x0, x1, y0, y1;
+    adj_span(tx, T.nx_tiles, kAdjTX, T.last_x0, G.nx, x0, x1);
+    adj_span(ty, T.ny_tiles, kAdjTY, T.last_y0, G.ny, y0, y1);
+    const int me = threadIdx.x;
+    const int x = x0 + me % kAdjTX, y = y0 + me / kAdjTX;
+    const bool active = x < x1 && y < y1;
+    const bool onW = G.wallW && x == 0, onE = G.wallE && x == G.nx - 1;
+    const bool onS = G.wallS && y == 0, onN = G.wallN && y == G.ny - 1;
+    const bool wall = onW || onE || onS || onN;
+    const int P1 = G.plane;
+    const AdjSlots<S> sl(G, active ? x : 0, active ? y : 0);
+    const unsigned og = (unsigned(y) * unsigned(G.pitch) + unsigned(x)) * unsigned(sizeof(double));
+
+    AdjNode<R> w;
+    // the gradient planes are read before the barrier, which global loads do not cross, so
+    // that their latency hides behind the step's arithmetic
+    double gphi0 = 0, gK0 = 0;
+    if (active) {
+        gphi0 = at(gphi, og);
+        if (!wall) gK0 = at(gK, og);
+        R lout[14];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) lam_out[i * G.plane + sy[i] * G.pitch + sx[i]] = S(af[i]);
+        for (int i = 0; i < 14; ++i) lout[i] = R(at(plane(lam_in, i, P1), sl.o[0]));
+        adj_open<S, R, PN>(state, med, G, P, x, y, onW, onE, onS, onN, lout, w);
+        if (wall) {
+            adj_hand_over<R>(w, [&](int i, R v) { handoff[i][me] = v; });
+            const bool okx_m = !onW, okx_p = !onE, oky_m = !onS, oky_p = !onN;
+            const bool ok[9] = {true, okx_m, oky_m, okx_p, oky_p, okx_m && oky_m,
+                                okx_p && oky_m, okx_p && oky_p, okx_m && oky_p};
 #pragma unroll
-    for (int i = 0; i < 5; ++i) lam_out[(9 + i) * G.plane + sy[i] * G.pitch + sx[i]] = S(ag[i]);
-    gphi[o] = gphi0 + double(lphi);
-    gK[o] = gK0 + double(lK);
+            for (int i = 0; i < 9; ++i)
+                if (ok[i]) at(plane(lam_out, i, P1), sl.o[i]) = S(0);
+#pragma unroll
+            for (int i = 0; i < 5; ++i)
+                if (ok[i]) at(plane(lam_out, 9 + i, P1), sl.o[i]) = S(0);
+            at(gphi, og) = gphi0 + double(w.lphib);
+        }
+    }
+    __syncthreads();
+    if (!active || wall) return;
+    R lphi, lK;
+    adj_close<R>(G, P, x, y, w, lphi, lK, [&](int i, int dx, int dy) {
+        return handoff[i][me + dy * kAdjTX + dx];
+    });
+#pragma unroll
+    for (int i = 0; i < 9; ++i) at(plane(lam_out, i, P1), sl.o[i]) = S(w.af[i]);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) at(plane(lam_out, 9 + i, P1), sl.o[i]) = S(w.ag[i]);
+    at(gphi, og) = gphi0 + double(lphi);
+    at(gK, og) = gK0 + double(lK);
+}
+
+// kAdjSteps backward steps per launch, bitwise as that many launches of adjoint_step_kernel would
+// take them (FP32): the adjoint of a tile of kAdjSide^2 nodes and its halo stays in LDS from step
+// to step.  On a small grid a backward step is latency, not work: at 256^2 its kernel took 6.8 us
+// (7.8 with the gap to the next), of which the arithmetic of one wavefront per SIMD is a quarter;
+// the launch and the round trip of the adjoint through memory are paid once per launch here.  The dataflow is the forward tile's with the arrows turned round: node x writes slot
+// (i, x - e_i), so a node may take step s when its neighbours took step s - 1, and step 1 covers
+// the tile and kAdjSteps - 1 nodes more on each open side.  A wall node and its inward neighbour
+// need each other within a step, so a region that would stop one node short of a wall takes the
+// wall in.  The forward states of the steps come from the recomputed segment; hand-offs are
+// indexed by the wall nodes' place along the region's sides; the gradient's sums are kept in LDS
+// and take each step's terms in the order of single steps.
+constexpr int kAdjRegion = kAdjSide + 2 * (kAdjSteps - 1) + 2;   // region side at most
+constexpr int kAdjTileThreads = (kAdjRegion * kAdjRegion + 63) / 64 * 64;
+constexpr int kAdjRow = kAdjRegion + 2;   // row of the adjoint in LDS: a margin on each side takes
+                                          // the slots of the region's edge nodes that nobody reads
+
+template <typename S>
+struct AdjStates {
+    const S* X[kAdjSteps];   // forward states of steps 1, 2, ... (backward in time)
+};
+
+template <typename S, typename R>
+constexpr size_t adjoint_tile_lds() {
+    return 2 * kAdjSide * kAdjSide * sizeof(double) + kHandoff * 4 * kAdjRegion * sizeof(R) +
+           14 * size_t(kAdjRow) * kAdjRow * sizeof(S);
+}
+
+template <typename S, typename R, bool PN>
+__global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
+    AdjStates<S> X, const S* __restrict__ lam_in, S* __restrict__ lam_out,
+    const S* __restrict__ med, double* __restrict__ gphi, double* __restrict__ gK, Geo G,
+    Phys<R> P, int tiles_x) {
+    constexpr int TS = kAdjSide, W = kAdjRegion, LW = kAdjRow, L = LW * LW, K = kAdjSteps;
+    extern __shared__ __align__(16) unsigned char adj_lds[];
+    double* const grad = reinterpret_cast<double*>(adj_lds);           // [2][TS * TS]
+    R* const hand = reinterpret_cast<R*>(grad + 2 * TS * TS);          // [kHandoff][4 * W]
+    S* const lam = reinterpret_cast<S*>(hand + kHandoff * 4 * W);      // [14][L]
+
+    const int t = tile_index(), ty = t / tiles_x, tx = t - ty * tiles_x;
+    const int x0 = tx * TS, y0 = ty * TS;
+    const int x1 = min(x0 + TS, G.nx), y1 = min(y0 + TS, G.ny);
+    int rx0 = x0 - (K - 1), rx1 = x1 + K - 1, ry0 = y0 - (K - 1), ry1 = y1 + K - 1;
+    int openW = 1, openE = 1, openS = 1, openN = 1;
+    if (G.wallW && rx0 <= 1) { rx0 = 0; openW = 0; }
+    if (G.wallE && rx1 >= G.nx - 1) { rx1 = G.nx; openE = 0; }
+    if (G.wallS && ry0 <= 1) { ry0 = 0; openS = 0; }
+    if (G.wallN && ry1 >= G.ny - 1) { ry1 = G.ny; openN = 0; }
+    const int RW = rx1 - rx0, RH = ry1 - ry0;   // at most W each
+
+    // slots whose owner lies beyond a wall are never written and read as zero
+    for (int k = threadIdx.x; k < 14 * L; k += kAdjTileThreads) lam[k] = S(0);
+
+    const int me = threadIdx.x;
+    const float fme = float(me) + 0.5f;
+#pragma unroll 1
+    for (int s = 1; s <= K; ++s) {
+        // the active nodes, dealt row by row as in the forward tile
+        const int ax = openW ? s - 1 : 0, ay = openS ? s - 1 : 0;
+        const int aw = RW - (openE ? s - 1 : 0) - ax, ah = RH - (openN ? s - 1 : 0) - ay;
+        const int row = int(fme * __builtin_amdgcn_rcpf(float(aw)));
+        const bool mine = row < ah;
+        const int lx = ax + me - row * aw, ly = ay + row;
+        const int ux = rx0 + lx, uy = ry0 + ly;   // unwrapped
+        int x = ux, y = uy;
+        if (!G.wallW) { x %= G.nx; x += x < 0 ? G.nx : 0; }
+        if (!G.wallS) { y %= G.ny; y += y < 0 ? G.ny : 0; }
+        const bool onW = G.wallW && x == 0, onE = G.wallE && x == G.nx - 1;
+        const bool onS = G.wallS && y == 0, onN = G.wallN && y == G.ny - 1;
+        const bool wall = onW || onE || onS || onN;
+        const bool inner = mine && ux >= x0 && ux < x1 && uy >= y0 && uy < y1;
+        const unsigned on = unsigned(y) * unsigned(G.pitch) + unsigned(x);
+        const unsigned og = on * unsigned(sizeof(double));
+        const int c = (ly + 1) * LW + lx + 1, tn = (uy - y0) * TS + (ux - x0);
+        double gphi0 = 0, gK0 = 0;
+        AdjNode<R> w;
+        if (mine) {
+            R lout[14];
+            if (s == 1) {
+                if (inner) {
+                    gphi0 = at(gphi, og);
+                    if (!wall) gK0 = at(gK, og);
+                }
+#pragma unroll
+                for (int i = 0; i < 14; ++i)
+                    lout[i] = R(at(plane(lam_in, i, G.plane), on * unsigned(sizeof(S))));
+            } else {
+                if (inner) {
+                    gphi0 = grad[tn];
+                    if (!wall) gK0 = grad[TS * TS + tn];
+                }
+#pragma unroll
+                for (int i = 0; i < 14; ++i) lout[i] = R(lam[i * L + c]);
+            }
+            adj_open<S, R, PN>(X.X[s - 1], med, G, P, x, y, onW, onE, onS, onN, lout, w);
+            if (wall) {
+                const int j = onW ? ly : onE ? W + ly : onS ? 2 * W + lx : 3 * W + lx;
+                adj_hand_over<R>(w, [&](int i, R v) { hand[i * 4 * W + j] = v; });
+            }
+        }
+        __syncthreads();   // hand-offs written, the adjoint read
+        if (mine) {
+            R lphi = R(0), lK = R(0);
+            if (!wall)
+                adj_close<R>(G, P, x, y, w, lphi, lK, [&](int i, int dx, int dy) {
+                    const int j = dx < 0 ? ly + dy : dx > 0 ? W + ly + dy
+                                               : dy < 0 ? 2 * W + lx : 3 * W + lx;
+                    return hand[i * 4 * W + j];
+                });
+            if (wall) {   // the forward step never reads a wall node's own slots
+#pragma unroll
+                for (int i = 0; i < 9; ++i) w.af[i] = R(0);
+#pragma unroll
+                for (int i = 0; i < 5; ++i) w.ag[i] = R(0);
+                lphi = w.lphib;
+            }
+            const double gp = gphi0 + double(lphi), gk = gK0 + double(lK);
+            if (s < K) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) lam[i * L + c - kEy[i] * LW - kEx[i]] = S(w.af[i]);
+#pragma unroll
+                for (int i = 0; i < 5; ++i)
+                    lam[(9 + i) * L + c - kEy[i] * LW - kEx[i]] = S(w.ag[i]);
+                if (inner) {
+                    grad[tn] = gp;
+                    if (!wall) grad[TS * TS + tn] = gk;
+                }
+            } else if (inner) {
+                const AdjSlots<S> sl(G, x, y);
+                const bool ok[9] = {true, !onW, !onS, !onE, !onN, !onW && !onS, !onE && !onS,
+                                    !onE && !onN, !onW && !onN};
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    if (ok[i]) at(plane(lam_out, i, G.plane), sl.o[i]) = S(w.af[i]);
+#pragma unroll
+                for (int i = 0; i < 5; ++i)
+                    if (ok[i]) at(plane(lam_out, 9 + i, G.plane), sl.o[i]) = S(w.ag[i]);
+                at(gphi, og) = gp;
+                if (!wall) at(gK, og) = gk;
+            }
+        }
+        if (s < K) __syncthreads();
+    }
 }
 
 // Seed: adjoint of X^N for J = Nu_hot(T at time N).  T(x) = T0 + sum_i g_i(x - e_i) at a fluid
@@ -490,6 +690,40 @@ hipError_t launch_adjoint_step(const void* state, const void* lam_in, void* lam_
     return hipGetLastError();
 }
 
+// Where kAdjSteps backward steps per launch beat one (us per step of lbm_grad, FP32, one / three:
+// 64^2 9.2 / 7.3, 128^2 9.4 / 7.0, 256^2 8.8 / 7.6, 320^2 10.9 / 10.4, 384^2 13.8 / 14.4, 1024^2
+// 62.6 / 69.3): up to about 320^2, where the launch costs more than the halo's redundant work
+// (1.27 times the tile's nodes).  With FP64 arithmetic a step is 1,100 instructions of a register-
+// and scalar-bound kernel, and one per launch is as fast or faster from 48^2 on (64^2 9.8 / 9.6,
+// 256^2 11.5 / 11.8; FP32 storage 8.9 / 9.2, 9.4 / 10.7), so there is no such form.
+template <typename S, typename R>
+bool adjoint_by_tiles(const Geo& G) {
+    return sizeof(R) == 4 && (long long)G.nx * G.ny <= 110000;
+}
+
+template <typename S, typename R>
+hipError_t launch_adjoint_tiles(const void* const states[kAdjSteps], const void* lam_in,
+                                void* lam_out, const void* med, double* gphi, double* gK,
+                                const Geo& G, const Phys<R>& P, hipStream_t s) {
+    if constexpr (sizeof(R) == 4) {
+        AdjStates<S> X;
+        for (int k = 0; k < kAdjSteps; ++k) X.X[k] = (const S*)states[k];
+        const int tiles_x = (G.nx + kAdjSide - 1) / kAdjSide;
+        const int nwg = tiles_x * ((G.ny + kAdjSide - 1) / kAdjSide);
+        constexpr size_t lds = adjoint_tile_lds<S, R>();
+        static_assert(lds <= 160 * 1024, "adjoint region exceeds the LDS of a CU");
+        if (med)
+            adjoint_tile_kernel<S, R, true><<<nwg, kAdjTileThreads, lds, s>>>(
+                X, (const S*)lam_in, (S*)lam_out, (const S*)med, gphi, gK, G, P, tiles_x);
+        else
+            adjoint_tile_kernel<S, R, false><<<nwg, kAdjTileThreads, lds, s>>>(
+                X, (const S*)lam_in, (S*)lam_out, nullptr, gphi, gK, G, P, tiles_x);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+
 template <typename R>
 hipError_t launch_fill(void* dst, size_t n, hipStream_t s) {
     fill_zero_kernel<R><<<1024, 256, 0, s>>>((R*)dst, n);
@@ -512,7 +746,11 @@ hipError_t launch_unpitch_scale(double* dst, const double* src, const Geo& G, do
                                                   const Phys<R>&, double, hipStream_t);          \
     template hipError_t launch_adjoint_step<S, R>(const void*, const void*, void*, const void*,  \
                                                   double*, double*, const Geo&, const Phys<R>&,  \
-                                                  hipStream_t);
+                                                  hipStream_t);                                  \
+    template hipError_t launch_adjoint_tiles<S, R>(const void* const*, const void*, void*,       \
+                                                   const void*, double*, double*, const Geo&,    \
+                                                   const Phys<R>&, hipStream_t);                 \
+    template bool adjoint_by_tiles<S, R>(const Geo&);
 LBM_ADJ_INSTANCES(float, float)
 LBM_ADJ_INSTANCES(double, double)
 LBM_ADJ_INSTANCES(float, double)

@@ -53,6 +53,13 @@ __device__ __forceinline__ T& at(T* base, unsigned byte_off) {
                                  byte_off);
 }
 
+// Tile of work-group blockIdx.x: each XCD (work-groups are dealt to the 8 of them in turn) takes a
+// contiguous run of the tiles.
+__device__ __forceinline__ int tile_index() {
+    const int n = gridDim.x, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    return xcd * (n / 8) + min(xcd, n % 8) + slot;
+}
+
 template <typename R>
 struct Phys {
     R rho0, inv_rho0;

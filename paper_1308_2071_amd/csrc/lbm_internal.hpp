@@ -59,7 +59,11 @@ int default_steps(const Geo& G, bool per_node_medium);
 template <typename S, typename R>
 hipError_t launch_tile_step(const void* src, void* dst, const void* med, const Geo& G,
                             const Phys<R>& P, int k, hipStream_t s);
-// Rows per tile and work-groups per launch of that kernel
+// The same, keeping every state: step s at dst + (s - 1) * stride (elements)
+template <typename S, typename R>
+hipError_t launch_tile_trace(const void* src, void* dst, size_t stride, const void* med,
+                             const Geo& G, const Phys<R>& P, int k, hipStream_t s);
+// Rows per tile and work-groups per launch of launch_tile_step
 template <typename S, typename R>
 void tile_shape(const Geo& G, int k, int* rows, int* nwg);
 // AA-pattern step in place; parity 0: the state is in the kAAOpp form, 1: kAAOwn
@@ -89,6 +93,16 @@ template <typename S, typename R>
 hipError_t launch_adjoint_step(const void* state, const void* lam_in, void* lam_out,
                                const void* med, double* gphi, double* gK, const Geo& G,
                                const Phys<R>& P, hipStream_t s);
+// Whether kAdjSteps backward steps per launch are faster than one (FP32, small grids)
+template <typename S, typename R>
+bool adjoint_by_tiles(const Geo& G);
+// kAdjSteps backward steps in one launch, each tile of kAdjSide^2 nodes in LDS; states: X^n,
+// X^{n-1}, ...; lam_in: adjoint of X^{n+1}; lam_out: adjoint of the last of the states
+constexpr int kAdjSide = 16, kAdjSteps = 3;
+template <typename S, typename R>
+hipError_t launch_adjoint_tiles(const void* const states[kAdjSteps], const void* lam_in,
+                                void* lam_out, const void* med, double* gphi, double* gK,
+                                const Geo& G, const Phys<R>& P, hipStream_t s);
 template <typename R>
 hipError_t launch_fill(void* dst, size_t n, hipStream_t s);
 hipError_t launch_fill_f64(double* dst, size_t n, hipStream_t s);

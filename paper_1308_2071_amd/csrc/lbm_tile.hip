@@ -33,6 +33,16 @@ LBM_TILE_KERNEL(tb3_step_kernel)    // three
 LBM_TILE_KERNEL(tb2_step_kernel)    // two
 #undef LBM_TILE_KERNEL
 
+// F::K steps that keep every state, step s at dst + (s - 1) * stride.
+template <typename S, typename R, bool PN, typename F>
+__global__ __launch_bounds__(F::NT, (F::template waves<R>())) void tile_trace_kernel(
+    const S* __restrict__ src, S* __restrict__ dst, size_t stride, const S* __restrict__ med,
+    Geo G, Phys<R> P, int tiles_x) {
+    const int t = tile_index(), ty = t / tiles_x;
+    tile_steps_body<S, R, PN, F::TX, F::TY, F::K, F::NT, true>(src, dst, med, G, P,
+                                                               t - ty * tiles_x, ty, stride);
+}
+
 // Steps per launch of the time loop by default.  The halo's redundant work grows with the steps
 // and shrinks with the tile, the launches and the bytes per step fall with the steps.  Measured,
 // us per step on porous cavities, uniform / per-node medium:
@@ -138,11 +148,35 @@ hipError_t launch_tile_step(const void* src, void* dst, const void* med, const G
     });
 }
 
+template <typename S, typename R, bool PN, typename F>
+static hipError_t launch_trace(const void* src, void* dst, size_t stride, const void* med,
+                               const Geo& G, const Phys<R>& P, int tiles_x, int nwg,
+                               hipStream_t s) {
+    constexpr size_t lds = tile_lds_bytes<S, R, PN, F::TX, F::TY, F::K>();
+    tile_trace_kernel<S, R, PN, F><<<nwg, F::NT, lds, s>>>((const S*)src, (S*)dst, stride,
+                                                           (const S*)med, G, P, tiles_x);
+    return hipGetLastError();
+}
+
+template <typename S, typename R>
+hipError_t launch_tile_trace(const void* src, void* dst, size_t stride, const void* med,
+                             const Geo& G, const Phys<R>& P, int k, hipStream_t s) {
+    if (k != 2 && k != 3 && k != kTileSteps && k != kTinyTileSteps) return hipErrorInvalidValue;
+    return with_form<S, R>(G, k, [&](auto f, int tiles_x, int nwg) {
+        using F = decltype(f);
+        return med ? launch_trace<S, R, true, F>(src, dst, stride, med, G, P, tiles_x, nwg, s)
+                   : launch_trace<S, R, false, F>(src, dst, stride, nullptr, G, P, tiles_x, nwg,
+                                                  s);
+    });
+}
+
 #define LBM_TILE_INST(S, R)                                                                    \
     template int default_steps<S, R>(const Geo&, bool);                                        \
     template void tile_shape<S, R>(const Geo&, int, int*, int*);                               \
     template hipError_t launch_tile_step<S, R>(const void*, void*, const void*, const Geo&,    \
-                                               const Phys<R>&, int, hipStream_t);
+                                               const Phys<R>&, int, hipStream_t);              \
+    template hipError_t launch_tile_trace<S, R>(const void*, void*, size_t, const void*,       \
+                                                const Geo&, const Phys<R>&, int, hipStream_t);
 LBM_TILE_INST(float, float)
 LBM_TILE_INST(double, double)
 LBM_TILE_INST(float, double)

@@ -62,18 +62,13 @@ __device__ __forceinline__ int tile_wrap(int r, int n, bool periodic) {
     return r < 0 ? r + n : r;
 }
 
-// Tile of work-group blockIdx.x: each XCD (work-groups are dealt to the 8 of them in turn) takes a
-// contiguous run of the tiles.
-__device__ __forceinline__ int tile_index() {
-    const int n = gridDim.x, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    return xcd * (n / 8) + min(xcd, n % 8) + slot;
-}
-
-// K steps of tile (tx, ty); NT: work-items per work-group.
-template <typename S, typename R, bool PN, int TX, int TY, int K, int NT>
+// K steps of tile (tx, ty) from src to dst; NT: work-items per work-group.  EVERY: the states in
+// between are kept too, step s at dst + (s - 1) * stride (elements); otherwise stride is unused.
+template <typename S, typename R, bool PN, int TX, int TY, int K, int NT, bool EVERY = false>
 __device__ __forceinline__ void tile_steps_body(const S* __restrict__ src, S* __restrict__ dst,
                                                 const S* __restrict__ med, const Geo& G,
-                                                const Phys<R>& P, int tx, int ty) {
+                                                const Phys<R>& P, int tx, int ty,
+                                                size_t stride = 0) {
     using Reg = TileRegion<TX, TY, K>;
     constexpr int W = Reg::W, L = Reg::N;
     static_assert(L <= NT, "one work-item per region node in step 1");
@@ -131,6 +126,19 @@ __device__ __forceinline__ void tile_steps_body(const S* __restrict__ src, S* __
         collide<R>(f, g, m, md, P);
     };
 
+    // this work-item's node, if it is the tile's, to the state of step s in global memory;
+    // unwrapped: the tile lies inside the grid
+    auto store = [&](int s, const R f[9], const R g[5]) {
+        const int x = rx0 + lx, y = ry0 + ly;
+        if (x < x0 || x >= x1 || y < y0 || y >= y1) return;
+        S* const to = dst + (EVERY ? size_t(s - 1) * stride : 0);
+        const unsigned o = (unsigned(y) * unsigned(G.pitch) + unsigned(x)) * unsigned(sizeof(S));
+#pragma unroll
+        for (int p = 0; p < 9; ++p) at(plane(to, p, G.plane), o) = S(f[p]);
+#pragma unroll
+        for (int p = 0; p < 5; ++p) at(plane(to, 9 + p, G.plane), o) = S(g[p]);
+    };
+
     // step 1, from the step-n buffer to LDS
     deal(1);
     if (mine) {
@@ -155,6 +163,7 @@ __device__ __forceinline__ void tile_steps_body(const S* __restrict__ src, S* __
         for (int p = 0; p < 9; ++p) A[p * L + c] = S(f[p]);
 #pragma unroll
         for (int p = 0; p < 5; ++p) A[(9 + p) * L + c] = S(g[p]);
+        if constexpr (EVERY) store(1, f, g);
     }
     __syncthreads();
 
@@ -195,21 +204,18 @@ __device__ __forceinline__ void tile_steps_body(const S* __restrict__ src, S* __
             for (int p = 0; p < 9; ++p) A[p * L + c] = S(f[p]);
 #pragma unroll
             for (int p = 0; p < 5; ++p) A[(9 + p) * L + c] = S(g[p]);
+            if constexpr (EVERY) store(s, f, g);
         }
         __syncthreads();
     }
 
-    // step K, from LDS to the other buffer; unwrapped: the tile lies inside the grid
+    // step K, from LDS to the other buffer
     deal(K);
     const int x = rx0 + lx, y = ry0 + ly;
     if (mine && x >= x0 && x < x1 && y >= y0 && y < y1) {
         R f[9], g[5];
         take(f, g);
-        const unsigned o = (unsigned(y) * unsigned(G.pitch) + unsigned(x)) * unsigned(sizeof(S));
-#pragma unroll
-        for (int p = 0; p < 9; ++p) at(plane(dst, p, G.plane), o) = S(f[p]);
-#pragma unroll
-        for (int p = 0; p < 5; ++p) at(plane(dst, 9 + p, G.plane), o) = S(g[p]);
+        store(K, f, g);
     }
 }
 
