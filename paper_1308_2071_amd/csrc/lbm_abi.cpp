@@ -1250,10 +1250,10 @@ lbm_status lbm_grad(lbm_ctx* c, double dJ, void* dJ_dphi, void* dJ_dK) {
                 "adjoint seed");
         const int64_t nseg = (N + C - 1) / C;
         // X^{n0} of segment sg is its checkpoint; X^{n0+1} .. X^{n0+len-1} are recomputed into
-        // bank sg % 2, as many steps per launch as the grid takes by default.
+        // bank sg % 2, several steps per launch where that pays.
         const int most = with_types(c->p.dtype, [&](auto stt, auto rt) {
             LBM_TYPES(stt, rt)
-            return default_steps<S, R>(c->G, c->med);
+            return recompute_steps<S, R>(c->G, c->med);
         });
         const bool by_tiles = with_types(c->p.dtype, [&](auto stt, auto rt) {
             LBM_TYPES(stt, rt)
@@ -1267,7 +1267,7 @@ lbm_status lbm_grad(lbm_ctx* c, double dJ, void* dJ_dphi, void* dJ_dK) {
             hipError_t e = hipSuccess;
             for (int64_t k = 0; k < len - 1 && e == hipSuccess;) {
                 const int64_t left = len - 1 - k;
-                const int m = left >= most ? most : left >= 2 ? 2 : 1;
+                const int m = left >= most ? most : left >= 2 && most > 1 ? 2 : 1;
                 e = m == 1 ? step_once(c, state(sg, k), state(sg, k + 1), aux)
                            : with_types(c->p.dtype, [&](auto stt, auto rt) {
                                  LBM_TYPES(stt, rt)

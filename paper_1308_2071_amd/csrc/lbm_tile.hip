@@ -82,6 +82,17 @@ int default_steps(const Geo& G, bool per_node_medium) {
     return per_node_medium && n >= 4096LL * 4096 ? 2 : 3;
 }
 
+// Steps per launch of the adjoint's recompute, which runs beside the backward sweep: the default,
+// except with FP64 arithmetic up to 256^2, where one backward step per launch sets the pace and a
+// tile's work-group holds up the sweep's longer than a single step's does (lbm_grad, us per step,
+// one / several recomputed per launch: FP64 96^2 9.5 / 9.7, 256^2 11.7 / 11.7; FP32 storage 128^2
+// 8.3 / 8.8, 256^2 9.1 / 9.9; FP64 320^2, where several pay, 17.2 / 15.8).
+template <typename S, typename R>
+int recompute_steps(const Geo& G, bool per_node_medium) {
+    if (sizeof(R) == 8 && (long long)G.nx * G.ny <= 256LL * 256) return 1;
+    return default_steps<S, R>(G, per_node_medium);
+}
+
 // Where two or three steps per launch take their larger tile: from the size on where the launch
 // has several rounds of work-groups, so that fewer, larger ones cost no balance (28 x 28 against
 // 28 x 12, FP32: 1024^2 12.1 against 11.3 us per step, 1536^2 23.5 against 22.4 and with a
@@ -172,6 +183,7 @@ hipError_t launch_tile_trace(const void* src, void* dst, size_t stride, const vo
 
 #define LBM_TILE_INST(S, R)                                                                    \
     template int default_steps<S, R>(const Geo&, bool);                                        \
+    template int recompute_steps<S, R>(const Geo&, bool);                                      \
     template void tile_shape<S, R>(const Geo&, int, int*, int*);                               \
     template hipError_t launch_tile_step<S, R>(const void*, void*, const void*, const Geo&,    \
                                                const Phys<R>&, int, hipStream_t);              \
