@@ -239,8 +239,8 @@ def leg_batched(torch, steps=10000):
             "bytes_per_node": BYTES_PER_NODE_FP32_UNIFORM,
             "shape": {"nodes_per_item": shape_keep[0], "wg": shape_keep[1],
                       "wgs": shape_keep[2], "graph_steps": shape_keep[3],
-                      "steps_per_launch": shape_keep[4], "rows_per_segment": shape_keep[5],
-                      "two_step_wgs": shape_keep[6], "two_step_strips_per_wg": shape_keep[7]},
+                      "steps_per_launch": shape_keep[4], "tile_rows": shape_keep[5],
+                      "tile_wgs": shape_keep[6], "tile_columns": shape_keep[7]},
             "plain_64_launches_per_step_mlups": round(seq, 1),
             "plain_per_cavity_graph_mlups": round(own, 1),
             "speedup_vs_plain_launches": round(mlups / seq, 2),

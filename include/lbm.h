@@ -249,7 +249,7 @@ lbm_status lbm_batch_workspace_size(int32_t n, const lbm_params* p, size_t* byte
  * (LBM_E_INVAL), a workspace too small (LBM_E_NOMEM) or a failed device call (LBM_E_HIP).
  * tune_cache_path: file where the launch shape picked by the
  * autotuner is cached per (device, dtype, cavity set); NULL disables tuning (default shape: two
- * steps per launch).  The autotuner also times one step per launch and keeps what is faster;
+ * or three steps per launch).  The autotuner times one and several steps per launch and keeps the fastest;
  * p[0].steps_per_launch = 1 or 2 forces one or two (the other cavities' values are ignored;
  * 2 gives LBM_E_UNSUPPORTED if a cavity's state reaches 2 GiB, a limit the autotuner's choice
  * does not have; 3, 4 and 8, forms of a single cavity, give LBM_E_UNSUPPORTED).  Results are
@@ -272,9 +272,9 @@ lbm_status lbm_batch_fields(lbm_ctx* c, int32_t i, void* ux, void* uy, void* p, 
 
 /* Launch shape in use (out holds 8 entries): out[0] nodes per work-item along x, out[1]
  * work-group size, out[2] work-groups per step of the one-step kernel, out[3] steps per graph
- * replay, out[4] time steps per launch (2 when the autotuner, steps_per_launch = 2 of the first
- * cavity or the default shape took the two-step kernel), out[5] rows of its tiles (0 if unused),
- * out[6] its work-groups per launch, out[7] w in its tiles' 64 / w - 2 columns. */
+ * replay, out[4] time steps per launch (more than 1 when the autotuner, steps_per_launch = 2 of
+ * the first cavity or the default shape took tiles in LDS), out[5] rows of those tiles (0 if
+ * unused), out[6] work-groups per launch in tiles, out[7] columns of a tile. */
 lbm_status lbm_batch_shape(const lbm_ctx* c, int32_t* out);
 
 /* ---------------------------------------------------------------------------------------- */

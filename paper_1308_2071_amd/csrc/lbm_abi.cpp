@@ -330,9 +330,10 @@ struct lbm_ctx {
     size_t b_state_bytes = 0, b_off_buf[2] = {0, 0}, b_off_cav = 0, b_off_phys = 0;
     size_t b_off_tiles = 0, b_off_part = 0, b_max_tiles = 0;
     int b_wg = 4, b_npt = 1, b_nwg = 0, b_ntiles = 0;   // b_wg: rows per tile
-    // two steps per launch: rows per tile (0: one step per launch), tiles to 64 columns, tiles
+    // several steps per launch: the tile (steps 0: one step per launch) and the number of tiles
     size_t b_off_cav2 = 0, b_off_tbwg = 0, b_max_tbwg = 0;
-    int b_tb_rows = 0, b_tb_nwg = 0, b_tb_per64 = 4;
+    BatchTile b_tile{};
+    int b_tb_nwg = 0;
 
     void* buf(int i) const { return ws + L.off_buf[i]; }
     void* medp() const { return med ? ws + L.off_med : nullptr; }
@@ -480,7 +481,11 @@ namespace {
 
 // ---- batched form ------------------------------------------------------------------------
 
-constexpr int kBatchGraphSteps = 32;   // even: a replay ends on the buffer it started from
+// An even number of launches at every steps-per-launch count: a replay ends on the buffer it
+// started from.
+constexpr int kBatchGraphSteps = 48;
+static_assert(kBatchGraphSteps % 4 == 0 && kBatchGraphSteps % 6 == 0 && kBatchGraphSteps % 8 == 0,
+              "kBatchGraphSteps must be an even number of launches of each form");
 // doubles per cavity: partial results, walls' sums, results
 constexpr int kBatchObsPer = kObsParts * kBatchObsWG + 2 * kNuWG + kObsOut;
 constexpr int kMinTileWidth = 64;      // narrowest tile of any supported launch shape
@@ -491,9 +496,8 @@ struct BatchLayout {
     size_t off_cav2, off_tbwg, max_tbwg;   // tables of the two-step form
 };
 
-// Work-groups of the batched two-step kernel with tiles of `rows` rows, per64 to 64 columns.
-size_t batch_tb_groups(const std::vector<Geo>& G, int rows, int per64) {
-    const int cols = batch_tb_cols(per64);
+// Tiles of `cols` x `rows` nodes that cover the cavities.
+size_t batch_tile_count(const std::vector<Geo>& G, int cols, int rows) {
     size_t n = 0;
     for (const Geo& g : G) n += size_t((g.nx + cols - 1) / cols) * size_t((g.ny + rows - 1) / rows);
     return n;
@@ -547,7 +551,7 @@ lbm_status batch_layout(int32_t n, const lbm_params* p, BatchLayout* L) {
     L->off_cav2 = o;
     o += align_up(n * sizeof(BatchCavity));
     L->off_tbwg = o;
-    L->max_tbwg = batch_tb_groups(geos, kBatchTbMinRows, 4);  // the most: the smallest tiles
+    L->max_tbwg = batch_tile_count(geos, kBatchMinCols, kBatchMinRows);  // the smallest tiles
     o += align_up(L->max_tbwg * sizeof(int));
     L->off_part = o;
     o += align_up(size_t(n) * kBatchObsPer * sizeof(double));
@@ -607,19 +611,15 @@ BatchTable<R> batch_table(const lbm_ctx* c) {
     return T;
 }
 
-// Tiles of the batched two-step kernel: rows, and how many of their regions make 64 columns.
-constexpr int kBatchTbRows[7] = {kBatchTbMinRows, 3, 4, 5, 6, 8, 12};
-constexpr int kBatchTbPer64[3] = {1, 2, 4};
-bool batch_tb_has(int rows, int per64) {
-    return std::count(kBatchTbRows, kBatchTbRows + 7, rows) > 0 &&
-           std::count(kBatchTbPer64, kBatchTbPer64 + 3, per64) > 0;
+// The tile with these rows and code (see BatchTile), or nullptr.
+const BatchTile* batch_tile(int rows, int code) {
+    for (const BatchTile& f : kBatchTiles)
+        if (f.rows == rows && f.code == code) return &f;
+    return nullptr;
 }
 
-// Tables of the two-step form for tiles of `rows` rows, per64 to 64 columns: per cavity its first
-// tile (tile0) and tiles along x, and the tile -> cavity list.
-hipError_t batch_tb_tables(lbm_ctx* c, int rows, int per64) {
-    if (!batch_tb_has(rows, per64)) return hipErrorInvalidValue;
-    const int cols = batch_tb_cols(per64);
+// Takes tile f: per cavity its first tile (tile0) and tiles along x, and the tile -> cavity list.
+hipError_t batch_take_tile(lbm_ctx* c, const BatchTile& f) {
     std::vector<BatchCavity> cav(c->ncav);
     std::vector<int> wc;
     for (int i = 0; i < c->ncav; ++i) {
@@ -627,10 +627,11 @@ hipError_t batch_tb_tables(lbm_ctx* c, int rows, int per64) {
         cav[i].G = G;
         cav[i].off = c->boff[i];
         cav[i].tile0 = int(wc.size());
-        cav[i].tiles_x = (G.nx + cols - 1) / cols;
-        wc.insert(wc.end(), size_t(cav[i].tiles_x) * size_t((G.ny + rows - 1) / rows), i);
+        cav[i].tiles_x = (G.nx + f.cols - 1) / f.cols;
+        wc.insert(wc.end(), size_t(cav[i].tiles_x) * size_t((G.ny + f.rows - 1) / f.rows), i);
     }
     if (wc.size() > c->b_max_tbwg) return hipErrorInvalidValue;
+    c->b_tile = f;
     c->b_tb_nwg = int(wc.size());
     hipError_t e = hipMemcpy(c->ws + c->b_off_cav2, cav.data(), cav.size() * sizeof(BatchCavity),
                              hipMemcpyHostToDevice);
@@ -650,14 +651,13 @@ BatchTable<R> batch_tb_table(const lbm_ctx* c) {
     return T;
 }
 
-// Two steps of every cavity in one launch, from buffer `from` to the other.
-hipError_t batch_step2(lbm_ctx* c, int from, hipStream_t s) {
+// c->b_tile.steps steps of every cavity in one launch, from buffer `from` to the other.
+hipError_t batch_steps(lbm_ctx* c, int from, hipStream_t s) {
     const void* src = c->ws + c->b_off_buf[from];
     void* dst = c->ws + c->b_off_buf[1 - from];
     return with_types(c->p.dtype, [&](auto st, auto rt) {
         LBM_TYPES(st, rt)
-        return launch_batch_tb2<S, R>(src, dst, batch_tb_table<R>(c), c->b_tb_rows,
-                                      c->b_tb_per64, s);
+        return launch_batch_tiles<S, R>(src, dst, batch_tb_table<R>(c), c->b_tile, s);
     });
 }
 
@@ -677,17 +677,11 @@ lbm_status ensure_batch_graph(lbm_ctx* c, int start) {
     HIP_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal), "begin capture");
     hipError_t err = hipSuccess;
     int b = start;
-    if (c->b_tb_rows > 0) {
-        // kBatchGraphSteps / 2 two-step launches: an even number of buffer swaps
-        for (int k = 0; k < kBatchGraphSteps / 2 && err == hipSuccess; ++k) {
-            err = batch_step2(c, b, c->cap);
-            b = 1 - b;
-        }
-    } else {
-        for (int k = 0; k < kBatchGraphSteps && err == hipSuccess; ++k) {
-            err = batch_step_once(c, b, c->cap);
-            b = 1 - b;
-        }
+    // an even number of buffer swaps
+    const int per = std::max(1, c->b_tile.steps);
+    for (int k = 0; k < kBatchGraphSteps / per && err == hipSuccess; ++k) {
+        err = per > 1 ? batch_steps(c, b, c->cap) : batch_step_once(c, b, c->cap);
+        b = 1 - b;
     }
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(c->cap, &graph);
@@ -734,10 +728,10 @@ std::string batch_key(const lbm_ctx* c) {
 }
 
 // A cache line: key, rows per tile, 64-node segments per work-item, work-groups (0: one tile
-// per work-group), rows per tile of the two-step form (0: one step per launch) and how many of
+// per work-group), rows per tile of the several-step form (0: one step per launch) and how many of
 // its tiles' regions make 64 columns.
 bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, int* nwg,
-                  int* tb_rows, int* tb_per64) {
+                  int* tb_rows, int* tb_code) {
     FILE* f = std::fopen(path, "r");
     if (!f) return false;
     char line[512], k[256];
@@ -749,7 +743,7 @@ bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, i
             *npt = b;
             *nwg = d;
             *tb_rows = t;
-            *tb_per64 = w;
+            *tb_code = w;
             found = true;
         }
     std::fclose(f);
@@ -757,10 +751,10 @@ bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, i
 }
 
 void cache_store(const char* path, const std::string& key, int wg, int npt, int nwg,
-                 int tb_rows, int tb_per64) {
+                 int tb_rows, int tb_code) {
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "%s %d %d %d %d %d\n", key.c_str(), wg, npt, nwg, tb_rows, tb_per64);
+    std::fprintf(f, "%s %d %d %d %d %d\n", key.c_str(), wg, npt, nwg, tb_rows, tb_code);
     std::fclose(f);
 }
 
@@ -783,14 +777,21 @@ hipError_t time_steps(lbm_ctx* c, hipEvent_t e0, hipEvent_t e1, int steps_per_la
 
 // Autotuner, on the batch itself.  The one-step kernel: every supported tile shape (rows per
 // work-group x 64-node segments per work-item), with one tile per work-group and with chunked
-// persistent grids of 2..16 work-groups per CU.  The two-step kernel: tiles of 2, 3, 4, 5, 6, 8
-// and 12 rows and 62, 30 or 14 columns.  It keeps the fastest per step (the one-step shape is
-// kept either way, for odd step counts), unless steps_per_launch of the first cavity forces one
-// or two steps per launch.  The result is cached per (device, dtype, cavity shapes, that setting)
-// in tune_cache_path.  Without a path, unless one step is asked for: two steps per launch in tiles
-// of 30 x 6 nodes, within 7 % of the best tile on batches of 300,000 to 5 million nodes (us per
-// step, FP32 / FP64: the 64-cavity workload 73.8 / 135 against 72.5 / 126, 8 cavities of 64^2 to
-// 250^2 5.7 / 8.8, the best; one step per launch took 102 / 213 and 11.1 / 20.1).
+// persistent grids of 2..16 work-groups per CU.  Several steps per launch: kBatchTiles, of which
+// those of three and four steps are for batches of kBatchManySteps nodes and more (smaller ones
+// keep the one or two steps per launch that lbm_batch_shape has always given for them).  It keeps
+// the fastest per step (the one-step shape is kept either way, for what is left of a step count),
+// unless steps_per_launch of the first cavity forces one or two steps per launch.  The result is
+// cached per (device, dtype, cavity shapes, that setting) in tune_cache_path.  Without a path,
+// unless one step is asked for: from kBatchManySteps nodes three steps in tiles of 28 x 12, below
+// two in tiles of 30 x 6.  us per step, FP32 / FP64 / FP32 storage with FP64 arithmetic:
+//                         one step      30 x 6 two      28 x 12 three   28 x 28 three
+//   64 cavities, 5.2 M    102 213 112   73.3 135 87.4   59.4 102 83.4   55.5 122 91.3
+//   40, 1.5 M             35 66 38      17.6 42.0 26.6  17.0 33.2 26.8  17.3 40.1 28.8
+//   4, 0.7 M              18 33 19      9.1 14.8 12.8   8.4 14.1 13.0   8.9 16.7 13.4
+//   8 of 64^2 to 250^2    11 20 12      5.7 8.8 8.0
+constexpr long long kBatchManySteps = 500000;
+
 lbm_status batch_tune(lbm_ctx* c, const char* path) {
     int cu = 256;
     int dev = 0;
@@ -799,19 +800,17 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
     const int spl = c->bp[0].steps_per_launch;
     const std::string key = batch_key(c) + "|s" + std::to_string(spl);
     int rows, npt, nwg, tbr, tbw;
-    c->b_tb_rows = 0;
+    long long nodes = 0;
+    for (const Geo& G : c->bG) nodes += (long long)G.nx * G.ny;
+    c->b_tile = BatchTile{};
     c->b_tb_nwg = 0;
     if (path && cache_lookup(path, key, &rows, &npt, &nwg, &tbr, &tbw) &&
-        (tbr == 0 || batch_tb_has(tbr, tbw))) {
+        (tbr == 0 || batch_tile(tbr, tbw))) {
         c->b_wg = rows;
         c->b_npt = npt;
         HIP_TRY(batch_tables(c, 64 * npt, rows), "tile tables");
         c->b_nwg = nwg > 0 ? nwg : c->b_ntiles;
-        if (tbr > 0) {
-            HIP_TRY(batch_tb_tables(c, tbr, tbw), "two-step tables");
-            c->b_tb_rows = tbr;
-            c->b_tb_per64 = tbw;
-        }
+        if (tbr > 0) HIP_TRY(batch_take_tile(c, *batch_tile(tbr, tbw)), "tile tables");
         return LBM_OK;
     }
     if (!path) {
@@ -820,9 +819,9 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
         HIP_TRY(batch_tables(c, 64, 4), "tile tables");
         c->b_nwg = c->b_ntiles;
         if (spl != 1) {
-            HIP_TRY(batch_tb_tables(c, 6, 2), "two-step tables");
-            c->b_tb_rows = 6;
-            c->b_tb_per64 = 2;
+            const bool many = spl == 0 && nodes >= kBatchManySteps;
+            HIP_TRY(batch_take_tile(c, many ? *batch_tile(12, 3) : *batch_tile(6, 2)),
+                    "tile tables");
         }
         return LBM_OK;
     }
@@ -833,7 +832,8 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
     HIP_TRY(hipEventCreate(&e0), "event");
     HIP_TRY(hipEventCreate(&e1), "event");
     float best = 1e30f, best_tb = 1e30f;
-    int br = 4, bn = 1, bg = 0, btr = 0, btw = 4;
+    int br = 4, bn = 1, bg = 0;
+    const BatchTile* bt = nullptr;
     lbm_status st = LBM_OK;
     for (const auto& sh : shapes) {
         hipError_t e = batch_tables(c, 64 * sh[1], sh[0]);
@@ -856,41 +856,31 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
         if (st != LBM_OK) break;
     }
     if (st == LBM_OK && spl != 1) {
-        for (int tr : kBatchTbRows) {
-            for (int tw : kBatchTbPer64) {
-                hipError_t e = batch_tb_tables(c, tr, tw);
-                if (e != hipSuccess) { st = hip_fail(e, "two-step tables"); break; }
-                c->b_tb_rows = tr;
-                c->b_tb_per64 = tw;
-                float ms = 0;
-                e = time_steps(c, e0, e1, 2,
-                               [&](int from) { return batch_step2(c, from, c->stream); }, &ms);
-                if (e != hipSuccess) { st = hip_fail(e, "autotune"); break; }
-                if (ms < best_tb) {
-                    best_tb = ms;
-                    btr = tr;
-                    btw = tw;
-                }
+        for (const BatchTile& f : kBatchTiles) {
+            if (f.steps > 2 && (spl == 2 || nodes < kBatchManySteps)) continue;
+            hipError_t e = batch_take_tile(c, f);
+            if (e != hipSuccess) { st = hip_fail(e, "tile tables"); break; }
+            float ms = 0;
+            e = time_steps(c, e0, e1, f.steps,
+                           [&](int from) { return batch_steps(c, from, c->stream); }, &ms);
+            if (e != hipSuccess) { st = hip_fail(e, "autotune"); break; }
+            if (ms < best_tb) {
+                best_tb = ms;
+                bt = &f;
             }
-            if (st != LBM_OK) break;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    c->b_tb_rows = 0;
+    c->b_tile = BatchTile{};
     if (st != LBM_OK) return st;
     c->b_wg = br;
     c->b_npt = bn;
     HIP_TRY(batch_tables(c, 64 * bn, br), "tile tables");
     c->b_nwg = bg > 0 ? bg : c->b_ntiles;
-    const int use_tr = (btr > 0 && (spl == 2 || best_tb < best)) ? btr : 0;
     c->b_tb_nwg = 0;
-    if (use_tr > 0) {
-        HIP_TRY(batch_tb_tables(c, use_tr, btw), "two-step tables");
-        c->b_tb_rows = use_tr;
-        c->b_tb_per64 = btw;
-    }
-    cache_store(path, key, br, bn, bg, use_tr, btw);
+    if (bt && (spl == 2 || best_tb < best)) HIP_TRY(batch_take_tile(c, *bt), "tile tables");
+    cache_store(path, key, br, bn, bg, c->b_tile.rows, bt ? bt->code : 1);
     return LBM_OK;
 }
 
@@ -1446,11 +1436,11 @@ lbm_status lbm_batch_step(lbm_ctx* c, int64_t nsteps) {
             c->step += kBatchGraphSteps;
         }
     }
-    if (c->b_tb_rows > 0) {
-        for (; left >= 2; left -= 2) {
-            HIP_TRY(batch_step2(c, c->cur, c->stream), "batch step launch");
+    if (const int per = c->b_tile.steps; per > 1) {
+        for (; left >= per; left -= per) {
+            HIP_TRY(batch_steps(c, c->cur, c->stream), "batch step launch");
             c->cur = 1 - c->cur;
-            c->step += 2;
+            c->step += per;
         }
     }
     for (; left > 0; --left) {
@@ -1537,10 +1527,10 @@ lbm_status lbm_batch_shape(const lbm_ctx* c, int32_t* out) {
     out[1] = 64 * c->b_wg;
     out[2] = c->b_nwg;
     out[3] = kBatchGraphSteps;
-    out[4] = c->b_tb_rows > 0 ? 2 : 1;
-    out[5] = c->b_tb_rows;
+    out[4] = std::max(1, c->b_tile.steps);
+    out[5] = c->b_tile.rows;
     out[6] = c->b_tb_nwg;
-    out[7] = c->b_tb_rows > 0 ? c->b_tb_per64 : 0;
+    out[7] = c->b_tile.cols;
     return LBM_OK;
 }
 

@@ -99,12 +99,12 @@ hipError_t launch_batch_step(const void* src, void* dst, const BatchTable<R>& T,
     }
 }
 
-// Two steps per launch for every cavity: tiles of TX x TY nodes in LDS as in the single cavity's
-// kernel, uniform medium per cavity.  The tiles of all cavities form one list, of which each XCD
+// K steps per launch for every cavity: tiles of TX x TY nodes in LDS as in the single cavity's
+// kernels, uniform medium per cavity.  The tiles of all cavities form one list, of which each XCD
 // takes a contiguous run: wg_cav[t] is the cavity of tile t, C.tile0 its first tile and C.tiles_x
 // its tiles along x.
-template <typename S, typename R, int TX, int TY, int NT>
-__global__ __launch_bounds__(NT, (sizeof(R) == 4 ? 6 : 4)) void batch_tb2_kernel(
+template <typename S, typename R, int TX, int TY, int K, int NT>
+__global__ __launch_bounds__(NT, (sizeof(R) == 8 ? 4 : NT > 896 ? 8 : 6)) void batch_tile_kernel(
     const S* __restrict__ src, S* __restrict__ dst, const BatchCavity* __restrict__ cav,
     const Phys<R>* __restrict__ phys, const int* __restrict__ wg_cav) {
     const int t = tile_index();
@@ -112,44 +112,52 @@ __global__ __launch_bounds__(NT, (sizeof(R) == 4 ? 6 : 4)) void batch_tb2_kernel
     const BatchCavity C = cav[c];
     const Phys<R> P = phys[c];
     const int lt = t - C.tile0, ty = lt / C.tiles_x;
-    tile_steps_body<S, R, false, TX, TY, 2, NT>(src + C.off, dst + C.off, (const S*)nullptr, C.G,
+    tile_steps_body<S, R, false, TX, TY, K, NT>(src + C.off, dst + C.off, (const S*)nullptr, C.G,
                                                 P, lt - ty * C.tiles_x, ty);
 }
 
-template <typename S, typename R, int TX, int TY>
-static hipError_t launch_tb2_v(const void* src, void* dst, const BatchTable<R>& T,
+template <typename S, typename R, int TX, int TY, int K>
+static hipError_t launch_tiles(const void* src, void* dst, const BatchTable<R>& T,
                                hipStream_t s) {
-    constexpr int NT = (TileRegion<TX, TY, 2>::N + 63) / 64 * 64;
-    constexpr size_t lds = tile_lds_bytes<S, R, false, TX, TY, 2>();
-    batch_tb2_kernel<S, R, TX, TY, NT><<<T.ntiles, NT, lds, s>>>((const S*)src, (S*)dst, T.cav,
-                                                                 T.phys, T.tile_cav);
+    constexpr int NT = (TileRegion<TX, TY, K>::N + 63) / 64 * 64;
+    constexpr size_t lds = tile_lds_bytes<S, R, false, TX, TY, K>();
+    static_assert(lds <= 160 * 1024, "tile region exceeds the LDS of a CU");
+    batch_tile_kernel<S, R, TX, TY, K, NT><<<T.ntiles, NT, lds, s>>>((const S*)src, (S*)dst,
+                                                                     T.cav, T.phys, T.tile_cav);
     return hipGetLastError();
 }
 
 template <typename S, typename R, int TY>
-static hipError_t launch_tb2_rows(const void* src, void* dst, const BatchTable<R>& T, int per64,
-                                  hipStream_t s) {
-    switch (per64) {
-        case 1: return launch_tb2_v<S, R, batch_tb_cols(1), TY>(src, dst, T, s);
-        case 2: return launch_tb2_v<S, R, batch_tb_cols(2), TY>(src, dst, T, s);
-        case 4: return launch_tb2_v<S, R, batch_tb_cols(4), TY>(src, dst, T, s);
+static hipError_t launch_two_steps(const void* src, void* dst, const BatchTable<R>& T, int cols,
+                                   hipStream_t s) {
+    switch (cols) {
+        case 62: return launch_tiles<S, R, 62, TY, 2>(src, dst, T, s);
+        case 30: return launch_tiles<S, R, 30, TY, 2>(src, dst, T, s);
+        case 14: return launch_tiles<S, R, 14, TY, 2>(src, dst, T, s);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <typename S, typename R>
-hipError_t launch_batch_tb2(const void* src, void* dst, const BatchTable<R>& T, int rows,
-                            int per64, hipStream_t s) {
-    switch (rows) {
-        case 2: return launch_tb2_rows<S, R, 2>(src, dst, T, per64, s);
-        case 3: return launch_tb2_rows<S, R, 3>(src, dst, T, per64, s);
-        case 4: return launch_tb2_rows<S, R, 4>(src, dst, T, per64, s);
-        case 5: return launch_tb2_rows<S, R, 5>(src, dst, T, per64, s);
-        case 6: return launch_tb2_rows<S, R, 6>(src, dst, T, per64, s);
-        case 8: return launch_tb2_rows<S, R, 8>(src, dst, T, per64, s);
-        case 12: return launch_tb2_rows<S, R, 12>(src, dst, T, per64, s);
-        default: return hipErrorInvalidValue;
+hipError_t launch_batch_tiles(const void* src, void* dst, const BatchTable<R>& T,
+                              const BatchTile& f, hipStream_t s) {
+    if (f.steps == 2) {
+        switch (f.rows) {
+            case 2: return launch_two_steps<S, R, 2>(src, dst, T, f.cols, s);
+            case 3: return launch_two_steps<S, R, 3>(src, dst, T, f.cols, s);
+            case 4: return launch_two_steps<S, R, 4>(src, dst, T, f.cols, s);
+            case 5: return launch_two_steps<S, R, 5>(src, dst, T, f.cols, s);
+            case 6: return launch_two_steps<S, R, 6>(src, dst, T, f.cols, s);
+            case 8: return launch_two_steps<S, R, 8>(src, dst, T, f.cols, s);
+            case 12: return launch_two_steps<S, R, 12>(src, dst, T, f.cols, s);
+        }
+    } else if (f.steps == 3 && f.cols == 28) {
+        if (f.rows == 12) return launch_tiles<S, R, 28, 12, 3>(src, dst, T, s);
+        if (f.rows == 28) return launch_tiles<S, R, 28, 28, 3>(src, dst, T, s);
+    } else if (f.steps == 4 && f.cols == 16 && f.rows == 16) {
+        return launch_tiles<S, R, 16, 16, 4>(src, dst, T, s);
     }
+    return hipErrorInvalidValue;
 }
 
 template hipError_t launch_batch_step<float, float>(const void*, void*, const BatchTable<float>&,
@@ -160,13 +168,13 @@ template hipError_t launch_batch_step<double, double>(const void*, void*,
 template hipError_t launch_batch_step<float, double>(const void*, void*,
                                                      const BatchTable<double>&, int, int, int,
                                                      hipStream_t);
-template hipError_t launch_batch_tb2<float, float>(const void*, void*, const BatchTable<float>&,
-                                                   int, int, hipStream_t);
-template hipError_t launch_batch_tb2<double, double>(const void*, void*,
-                                                     const BatchTable<double>&, int, int,
-                                                     hipStream_t);
-template hipError_t launch_batch_tb2<float, double>(const void*, void*,
-                                                    const BatchTable<double>&, int, int,
-                                                    hipStream_t);
+template hipError_t launch_batch_tiles<float, float>(const void*, void*, const BatchTable<float>&,
+                                                     const BatchTile&, hipStream_t);
+template hipError_t launch_batch_tiles<double, double>(const void*, void*,
+                                                       const BatchTable<double>&,
+                                                       const BatchTile&, hipStream_t);
+template hipError_t launch_batch_tiles<float, double>(const void*, void*,
+                                                      const BatchTable<double>&,
+                                                      const BatchTile&, hipStream_t);
 
 }  // namespace lbm

@@ -25,10 +25,19 @@ constexpr int kPlanePad = 1056;
 // Elements per plane: ny rows of the pitch, then the pad.
 inline long long plane_elems(long long pitch, long long ny) { return pitch * ny + kPlanePad; }
 
-// Two steps per launch of the batch: columns of a tile whose region (one node more on each side)
-// is 64 / per64 columns wide, and the fewest rows of a tile.
-constexpr int batch_tb_cols(int per64) { return 64 / per64 - 2; }
-constexpr int kBatchTbMinRows = 2;
+// Tiles of the batch: columns and rows, steps per launch, and the code that goes with the rows in
+// the tuner's cache (1, 2 and 4: two steps, a region of 64 / code columns; 3: more steps).
+struct BatchTile {
+    int cols, rows, steps, code;
+};
+constexpr BatchTile kBatchTiles[] = {
+    {62, 2, 2, 1}, {30, 2, 2, 2}, {14, 2, 2, 4}, {62, 3, 2, 1}, {30, 3, 2, 2}, {14, 3, 2, 4},
+    {62, 4, 2, 1}, {30, 4, 2, 2}, {14, 4, 2, 4}, {62, 5, 2, 1}, {30, 5, 2, 2}, {14, 5, 2, 4},
+    {62, 6, 2, 1}, {30, 6, 2, 2}, {14, 6, 2, 4}, {62, 8, 2, 1}, {30, 8, 2, 2}, {14, 8, 2, 4},
+    {62, 12, 2, 1}, {30, 12, 2, 2}, {14, 12, 2, 4},
+    {28, 12, 3, 3}, {28, 28, 3, 3}, {16, 16, 4, 3},
+};
+constexpr int kBatchMinCols = 14, kBatchMinRows = 2;
 
 // Tile side and steps per launch of the forms for small grids (lbm_tile.hip).
 constexpr int kTileSide = 16;
@@ -129,12 +138,12 @@ struct BatchTable {
     int ntiles;
 };
 
-// Two steps per launch for every cavity of a batch, in tiles of `rows` rows (2, 3, 4, 5, 6, 8 or
-// 12) and batch_tb_cols(per64) columns (per64 1, 2 or 4): T.tile_cav maps each of the T.ntiles
-// tiles to its cavity, whose tile0 is its first tile and tiles_x its tiles along x.
+// f.steps steps per launch for every cavity of a batch, in tiles f (one of kBatchTiles):
+// T.tile_cav maps each of the T.ntiles tiles to its cavity, whose tile0 is its first tile and
+// tiles_x its tiles along x.
 template <typename S, typename R>
-hipError_t launch_batch_tb2(const void* src, void* dst, const BatchTable<R>& T, int rows,
-                            int per64, hipStream_t s);
+hipError_t launch_batch_tiles(const void* src, void* dst, const BatchTable<R>& T,
+                              const BatchTile& f, hipStream_t s);
 
 // Observables of every cavity (no fields): results of cavity i at out[kObsOut * i]; part has room
 // for kObsParts * kBatchObsWG + 2 * kNuWG doubles per cavity; largest: nodes of the largest one.
