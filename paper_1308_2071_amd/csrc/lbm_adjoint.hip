@@ -223,26 +223,11 @@ __device__ __forceinline__ bool on_wall(const Geo& G, int x, int y) {
            (G.wallN && y == G.ny - 1);
 }
 
-// Work-group tiles of the backward step: kAdjTX x kAdjTY nodes, one work-item each, one
-// wavefront per row.  Every wall node shares its tile with its inward neighbour: where the
-// last tile along a walled axis would be one node wide, it starts one node earlier and the tile
-// before it ends there (a walled axis has at least five nodes).
+// Work-group tiles of the backward step, one work-item per node, one wavefront per row.
 constexpr int kAdjTX = 64, kAdjTY = 4, kAdjThreads = kAdjTX * kAdjTY;
 // What a wall node hands its inward neighbour: the adjoints of the neighbour's 14 pulled
 // populations and of its ux, uy, 1/phi, theta and P.
 constexpr int kHandoff = 19;
-
-struct AdjTiles {
-    int nx_tiles, ny_tiles;
-    int last_x0, last_y0;   // first column and first row of the last tile along x and y
-};
-
-// Nodes [a, b) of tile t of T along an axis of n nodes.
-__device__ __forceinline__ void adj_span(int t, int T, int side, int last0, int n, int& a,
-                                         int& b) {
-    a = t == T - 1 ? last0 : t * side;
-    b = t == T - 1 ? n : min((t + 1) * side, last0);
-}
 
 // A node's backward step up to the point where wall nodes hand their share over, and from there.
 template <typename R>
@@ -399,12 +384,12 @@ template <typename S, typename R, bool PN>
 __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
     const S* __restrict__ state, const S* __restrict__ lam_in, S* __restrict__ lam_out,
     const S* __restrict__ med, double* __restrict__ gphi, double* __restrict__ gK, Geo G,
-    Phys<R> P, AdjTiles T) {
+    Phys<R> P, WallTiles T) {
     __shared__ R handoff[kHandoff][kAdjThreads];
     const int t = tile_index(), ty = t / T.nx_tiles, tx = t - ty * T.nx_tiles;
     int x0, x1, y0, y1;
-    adj_span(tx, T.nx_tiles, kAdjTX, T.last_x0, G.nx, x0, x1);
-    adj_span(ty, T.ny_tiles, kAdjTY, T.last_y0, G.ny, y0, y1);
+    wall_span(tx, T.nx_tiles, kAdjTX, T.last_x0, G.nx, x0, x1);
+    wall_span(ty, T.ny_tiles, kAdjTY, T.last_y0, G.ny, y0, y1);
     const int me = threadIdx.x;
     const int x = x0 + me % kAdjTX, y = y0 + me / kAdjTX;
     const bool active = x < x1 && y < y1;
@@ -673,13 +658,7 @@ template <typename S, typename R>
 hipError_t launch_adjoint_step(const void* state, const void* lam_in, void* lam_out,
                                const void* med, double* gphi, double* gK, const Geo& G,
                                const Phys<R>& P, hipStream_t s) {
-    AdjTiles T;
-    T.nx_tiles = (G.nx + kAdjTX - 1) / kAdjTX;
-    T.ny_tiles = (G.ny + kAdjTY - 1) / kAdjTY;
-    T.last_x0 = (T.nx_tiles - 1) * kAdjTX;
-    T.last_y0 = (T.ny_tiles - 1) * kAdjTY;
-    if (G.wallE && G.nx - T.last_x0 == 1) T.last_x0 = G.nx - 2;
-    if (G.wallN && G.ny - T.last_y0 == 1) T.last_y0 = G.ny - 2;
+    const WallTiles T = wall_tiles(G, kAdjTX, kAdjTY);
     const int nwg = T.nx_tiles * T.ny_tiles;
     if (med)
         adjoint_step_kernel<S, R, true><<<nwg, kAdjThreads, 0, s>>>(

@@ -53,6 +53,32 @@ __device__ __forceinline__ T& at(T* base, unsigned byte_off) {
                                  byte_off);
 }
 
+// Tiles of TX x TY nodes in which every wall node shares its tile with its inward neighbour: where
+// the last tile along a walled axis would be one node wide, it starts one node earlier and the
+// tile before it ends there (a walled axis has at least five nodes).
+struct WallTiles {
+    int nx_tiles, ny_tiles;
+    int last_x0, last_y0;   // first column and first row of the last tile along x and y
+};
+
+inline WallTiles wall_tiles(const Geo& G, int TX, int TY) {
+    WallTiles T;
+    T.nx_tiles = (G.nx + TX - 1) / TX;
+    T.ny_tiles = (G.ny + TY - 1) / TY;
+    T.last_x0 = (T.nx_tiles - 1) * TX;
+    T.last_y0 = (T.ny_tiles - 1) * TY;
+    if (G.wallE && G.nx - T.last_x0 == 1) T.last_x0 = G.nx - 2;
+    if (G.wallN && G.ny - T.last_y0 == 1) T.last_y0 = G.ny - 2;
+    return T;
+}
+
+// Nodes [a, b) of tile t of T along an axis of n nodes.
+__device__ __forceinline__ void wall_span(int t, int T, int side, int last0, int n, int& a,
+                                          int& b) {
+    a = t == T - 1 ? last0 : t * side;
+    b = t == T - 1 ? n : min((t + 1) * side, last0);
+}
+
 // Tile of work-group blockIdx.x: each XCD (work-groups are dealt to the 8 of them in turn) takes a
 // contiguous run of the tiles.
 __device__ __forceinline__ int tile_index() {

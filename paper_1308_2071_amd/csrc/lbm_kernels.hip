@@ -14,11 +14,13 @@ template <typename S, typename R, bool PN>
 __global__ __launch_bounds__(kTileX) void step_kernel(const S* __restrict__ src,
                                                       S* __restrict__ dst,
                                                       const S* __restrict__ med, Geo G,
-                                                      Phys<R> P, int tiles_x) {
-    // Work-groups in launch order walk the lattice row by row.  (Dealing each XCD one
-    // contiguous band of rows instead was measured 7% slower: it concentrates each XCD's
-    // stream on one address range.)
-    const int t = blockIdx.x;
+                                                      Phys<R> P, int tiles_x, int by_xcd) {
+    // Work-groups in launch order walk the lattice row by row, or each XCD takes one contiguous
+    // band of rows: the latter for a state that the XCDs' 8 x 4 MiB of L2 hold (us per step: FP32
+    // 256^2 4.5 to 3.6, 512^2 7.9 to 7.0, FP64 256^2 5.7 to 4.5), not for a larger one, where it
+    // concentrates each XCD's stream on one address range (FP64 1536^2 100 to 104, FP32 4096^2 7 %
+    // slower).
+    const int t = by_xcd ? tile_index() : int(blockIdx.x);
     const int y = t / tiles_x;
     const int x = (t - y * tiles_x) * kTileX + threadIdx.x;
     if (x >= G.nx) return;
@@ -62,6 +64,36 @@ __global__ __launch_bounds__(kTileX) void aa_step_kernel(S* __restrict__ buf,
                                    });
     collide<R>(f, g, m, md, P);
     aa_store<S, R, L>(buf, G, x, y, f, g);
+}
+
+// The same step for states that fit the Infinity Cache (see aa_in_tiles): tiles of kAATX x kAATY
+// nodes in which a wall node, which pulls at its inward neighbour, shares the work-group of that
+// neighbour, which overwrites those slots; the work-group reads everything before it writes
+// anything.  A wall node costs its own wavefront a branch, where aa_step_kernel's wavefronts along
+// the walls step up to four nodes in turn (64^2 FP32 6.3 us per step against 3.6), and each XCD
+// takes a contiguous run of tiles, so that rows shared by neighbouring tiles stay in its L2
+// (1024^2 FP32 22.1 us per step, here 20.9 in launch order and 19.2 so).
+constexpr int kAATX = 128, kAATY = 2;
+template <typename S, typename R, bool PN, int L>
+__global__ __launch_bounds__(kAATX* kAATY) void aa_tile_step_kernel(S* buf,
+                                                                    const S* __restrict__ med,
+                                                                    Geo G, Phys<R> P,
+                                                                    WallTiles T) {
+    const int t = tile_index(), ty = t / T.nx_tiles, tx = t - ty * T.nx_tiles;
+    int x0, x1, y0, y1;
+    wall_span(tx, T.nx_tiles, kAATX, T.last_x0, G.nx, x0, x1);
+    wall_span(ty, T.ny_tiles, kAATY, T.last_y0, G.ny, y0, y1);
+    const int x = x0 + int(threadIdx.x) % kAATX, y = y0 + int(threadIdx.x) / kAATX;
+    const bool active = x < x1 && y < y1;
+    R f[9], g[5];
+    if (active) {
+        Mac<R> m;
+        Med<R> md;
+        node_state<R, PN, S, L>(buf, med, G, P, x, y, f, g, m, md);
+        collide<R>(f, g, m, md, P);
+    }
+    __syncthreads();   // every slot read before any is written
+    if (active) aa_store<S, R, L>(buf, G, x, y, f, g);
 }
 
 // Maximum and minimum that propagate a NaN (fmax and fmin would drop it), so that a
@@ -426,17 +458,50 @@ __global__ void pitch_copy_kernel(R* __restrict__ dst, const R* __restrict__ src
 
 // ---- launchers --------------------------------------------------------------------------------
 
+// Whether the AA step runs in tiles: for a state that fits the 256 MiB Infinity Cache, where the
+// XCDs' L2 hits matter more than the order in which memory is streamed.  us per step, rows in
+// launch order / tiles by XCD: FP32 64^2 6.3 / 3.6, 512^2 8.9 / 5.8, 1024^2 22.1 / 19.2, 2048^2
+// (235 MB) 74.8 / 69.3, 2500^2 127 / 136, 4096^2 353 / 366; FP64 128^2 6.8 / 4.9, 1536^2 (264 MB)
+// 83.2 / 78.2, 2000 x 1500 118 / 125, 4096^2 706 / 720.
+static size_t state_bytes(const Geo& G, size_t elem_bytes) {
+    return size_t(kPlanes) * size_t(G.plane) * elem_bytes;
+}
+static bool aa_in_tiles(const Geo& G, size_t elem_bytes) {
+    return state_bytes(G, elem_bytes) <= size_t(256) << 20;
+}
+
 template <typename S, typename R>
 hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G,
                        const Phys<R>& P, hipStream_t s) {
     const int tiles_x = (G.nx + kTileX - 1) / kTileX;
     const int nwg = tiles_x * G.ny;
+    const int by_xcd = state_bytes(G, sizeof(S)) <= size_t(32) << 20 ? 1 : 0;
     if (med)
         step_kernel<S, R, true><<<nwg, kTileX, 0, s>>>((const S*)src, (S*)dst, (const S*)med, G,
-                                                       P, tiles_x);
+                                                       P, tiles_x, by_xcd);
     else
         step_kernel<S, R, false><<<nwg, kTileX, 0, s>>>((const S*)src, (S*)dst, nullptr, G, P,
-                                                        tiles_x);
+                                                        tiles_x, by_xcd);
+    return hipGetLastError();
+}
+
+template <typename S, typename R, int L>
+static hipError_t aa_launch(S* b, const S* m, const Geo& G, const Phys<R>& P, hipStream_t s) {
+    if (aa_in_tiles(G, sizeof(S))) {
+        const WallTiles T = wall_tiles(G, kAATX, kAATY);
+        const int nwg = T.nx_tiles * T.ny_tiles;
+        if (m)
+            aa_tile_step_kernel<S, R, true, L><<<nwg, kAATX * kAATY, 0, s>>>(b, m, G, P, T);
+        else
+            aa_tile_step_kernel<S, R, false, L><<<nwg, kAATX * kAATY, 0, s>>>(b, m, G, P, T);
+    } else {
+        const int tiles_x = (G.nx + kTileX - 1) / kTileX;
+        const int nwg = tiles_x * G.ny;
+        if (m)
+            aa_step_kernel<S, R, true, L><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
+        else
+            aa_step_kernel<S, R, false, L><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
+    }
     return hipGetLastError();
 }
 
@@ -444,22 +509,8 @@ hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G
 template <typename S, typename R>
 hipError_t launch_aa_step(void* buf, const void* med, const Geo& G, const Phys<R>& P,
                           int parity, hipStream_t s) {
-    const int tiles_x = (G.nx + kTileX - 1) / kTileX;
-    const int nwg = tiles_x * G.ny;
-    S* b = (S*)buf;
-    const S* m = (const S*)med;
-    if (parity == 0) {
-        if (med)
-            aa_step_kernel<S, R, true, kAAOpp><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
-        else
-            aa_step_kernel<S, R, false, kAAOpp><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
-    } else {
-        if (med)
-            aa_step_kernel<S, R, true, kAAOwn><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
-        else
-            aa_step_kernel<S, R, false, kAAOwn><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
-    }
-    return hipGetLastError();
+    return parity == 0 ? aa_launch<S, R, kAAOpp>((S*)buf, (const S*)med, G, P, s)
+                       : aa_launch<S, R, kAAOwn>((S*)buf, (const S*)med, G, P, s);
 }
 
 // Work-groups and their size for the observables of n nodes: one node per work-item of 256 while
