@@ -889,11 +889,12 @@ lbm_status batch_tune(lbm_ctx* c, const char* path) {
 namespace {
 
 // Fills context c for the validated parameters p over the workspace (at least L.total bytes)
-// and puts the cavity at rest: the medium planes (when phi or K is given) and both state
-// buffers are written, so nothing in the workspace needs to start at zero.  Synchronises.
+// and enqueues the medium planes (when phi or K is given) and the state at rest, so nothing in
+// the workspace needs to start at zero.  `buffers`: state buffers to fill; the second holds no
+// state yet, and only its row padding, which no step writes and lbm_save copies, depends on it.
 lbm_status setup_ctx(lbm_ctx* c, const lbm_params& p, const Layout& L, int64_t nmax,
                      const void* phi, const void* K, double phi_uniform, void* workspace,
-                     void* hip_stream) {
+                     void* hip_stream, int buffers) {
     const bool med = phi != nullptr || K != nullptr;
     c->p = p;
     c->d = derive(p);
@@ -920,12 +921,10 @@ lbm_status setup_ctx(lbm_ctx* c, const lbm_params& p, const Layout& L, int64_t n
             if (e1 == hipSuccess)
                 e1 = launch_pitch_copy<S>(mp + plane_bytes, K, c->G, Kv, c->stream);
         }
-        // both buffers, so that the row padding (never written by a step) is defined too
-        for (int b = 0; b < 2 && e1 == hipSuccess; ++b)
+        for (int b = 0; b < buffers && e1 == hipSuccess; ++b)
             e1 = launch_rest<S>(c->buf(b), c->G, g0, g1, c->stream);
         return e1;
     });
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(e, "cavity set-up");
     return LBM_OK;
 }
@@ -1084,7 +1083,11 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, const void* phi, const v
         return fail(LBM_E_NOMEM, "workspace of %zu bytes < %zu needed", ws_bytes, L.total);
     lbm_ctx* c = new (std::nothrow) lbm_ctx();
     if (!c) return fail(LBM_E_NOMEM, "host allocation failed");
-    s = setup_ctx(c, *p, L, nmax, phi, K, phi_uniform, workspace, hip_stream);
+    s = setup_ctx(c, *p, L, nmax, phi, K, phi_uniform, workspace, hip_stream, 2);
+    if (s == LBM_OK) {   // the caller may free phi and K after the call
+        const hipError_t e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) s = hip_fail(e, "cavity set-up");
+    }
     if (s != LBM_OK) {
         delete c;
         return s;
@@ -1555,23 +1558,31 @@ lbm_status lbm_run_noalloc(const lbm_params* p, const void* phi, const void* K,
     s = scratch_address(&ws);
     if (s != LBM_OK) return s;
     lbm_ctx c;  // on the stack: no host allocation either
-    s = setup_ctx(&c, *p, L, 0, phi, K, phi_uniform, ws, hip_stream);
-    if (s != LBM_OK) return s;
-    int64_t left = nsteps;
-    const int k = launch_steps(&c);
-    if (k > 1) {
-        for (; left >= k; left -= k) {
-            HIP_TRY(advance_k(&c, k, c.cur, c.stream), "step launch");
-            c.cur = 1 - c.cur;
-            c.step += k;
+    // no wait after the set-up: the steps follow on the same stream, and the observables wait for
+    // all of it
+    auto run = [&]() -> lbm_status {
+        const lbm_status s0 = setup_ctx(&c, *p, L, 0, phi, K, phi_uniform, ws, hip_stream, 1);
+        if (s0 != LBM_OK) return s0;
+        int64_t left = nsteps;
+        const int k = launch_steps(&c);
+        if (k > 1) {
+            for (; left >= k; left -= k) {
+                HIP_TRY(advance_k(&c, k, c.cur, c.stream), "step launch");
+                c.cur = 1 - c.cur;
+                c.step += k;
+            }
         }
-    }
-    for (; left > 0; --left) {
-        HIP_TRY(advance(&c, c.cur, c.stream), "step launch");
-        c.cur = 1 - c.cur;
-        c.step += 1;
-    }
-    return observe_ctx(&c, o, ux, uy, pr, T);
+        for (; left > 0; --left) {
+            HIP_TRY(advance(&c, c.cur, c.stream), "step launch");
+            c.cur = 1 - c.cur;
+            c.step += 1;
+        }
+        return observe_ctx(&c, o, ux, uy, pr, T);
+    };
+    s = run();
+    // a failure part-way leaves nothing in flight on the caller's arrays
+    if (s != LBM_OK && s != LBM_E_DIVERGED) (void)hipStreamSynchronize(c.stream);
+    return s;
 }
 
 }  // extern "C"
