@@ -263,23 +263,11 @@ struct AdjSlots {
 __device__ constexpr int kEx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 __device__ constexpr int kEy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 
-// state: the forward state X^n (post-collision populations entering step n); lout: adjoint of
-// X^{n+1} in the node's own 14 slots; (x, y) in the grid.  A fluid node reverses its own
-// collision.  A wall node runs the same gather, macroscopics and collision VJP on its own
-// reconstructed state (so both kinds of node stay in step), then reverses the reconstruction.
+// The medium at (px, py), the node whose pulled populations a node's state is built from: itself,
+// or for a wall node its inward neighbour (the diagonal one at a corner).
 template <typename S, typename R, bool PN>
-__device__ __forceinline__ void adj_open(const S* __restrict__ state, const S* __restrict__ med,
-                                         const Geo& G, const Phys<R>& P, int x, int y, bool onW,
-                                         bool onE, bool onS, bool onN, const R lout[14],
-                                         AdjNode<R>& w) {
-    const bool wall = onW || onE || onS || onN;
-    // the node whose pulled populations this node's state is built from: itself, or its inward
-    // neighbour (the diagonal one at a corner)
-    const int px = x + (onW ? 1 : 0) - (onE ? 1 : 0);
-    const int py = y + (onS ? 1 : 0) - (onN ? 1 : 0);
-    R (&f)[9] = w.f;
-    R (&g)[5] = w.g;
-    pull<R, S>(state, G, px, py, f, g);
+__device__ __forceinline__ void adj_medium(const S* __restrict__ med, const Geo& G,
+                                           const Phys<R>& P, int px, int py, AdjNode<R>& w) {
     if constexpr (PN) {
         const unsigned op = (unsigned(py) * unsigned(G.pitch) + unsigned(px)) * unsigned(sizeof(S));
         w.phi = R(at(med, op));
@@ -290,6 +278,19 @@ __device__ __forceinline__ void adj_open(const S* __restrict__ state, const S* _
         w.K = P.c_lin > R(0) ? w.phi * P.nu / P.c_lin : R(INFINITY);
         w.md = Med<R>{P.phi, P.inv_phi, P.c_lin, P.c_nl};
     }
+}
+
+// w.f, w.g: the populations of the forward state X^n (post-collision, entering step n) pulled at
+// (px, py), with w's medium there; own_phi(): phi of a wall node itself; lout: adjoint of X^{n+1}
+// in the node's own 14 slots.  A fluid node reverses its own collision.  A wall node runs the same
+// macroscopics and collision VJP on its own reconstructed state (so both kinds of node stay in
+// step), then reverses the reconstruction.
+template <typename R, typename OwnPhi>
+__device__ __forceinline__ void adj_open(const Phys<R>& P, bool onW, bool onE, bool onS, bool onN,
+                                         const R lout[14], AdjNode<R>& w, OwnPhi&& own_phi) {
+    const bool wall = onW || onE || onS || onN;
+    R (&f)[9] = w.f;
+    R (&g)[5] = w.g;
     const Mac<R> m = fluid_macros<R>(f, g, w.md, P);
     Mac<R> mc = m;
     Med<R> mdc = w.md;
@@ -298,7 +299,7 @@ __device__ __forceinline__ void adj_open(const S* __restrict__ state, const S* _
         // the wall node's state: rebuilt from its neighbour's, at rest, with its own phi
         theta_b = wall_theta<R>(onW, onE, onS, onN, m.theta, P);
         nee_wall<R>(f, g, m, w.md, theta_b, P);
-        phi_b = PN ? R(med[size_t(y) * G.pitch + x]) : P.phi;
+        phi_b = own_phi();
         mc.theta = theta_b;
         mc.ux = R(0);
         mc.uy = R(0);
@@ -410,7 +411,12 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
         R lout[14];
 #pragma unroll
         for (int i = 0; i < 14; ++i) lout[i] = R(at(plane(lam_in, i, P1), sl.o[0]));
-        adj_open<S, R, PN>(state, med, G, P, x, y, onW, onE, onS, onN, lout, w);
+        const int px = x + (onW ? 1 : 0) - (onE ? 1 : 0);
+        const int py = y + (onS ? 1 : 0) - (onN ? 1 : 0);
+        pull<R, S>(state, G, px, py, w.f, w.g);
+        adj_medium<S, R, PN>(med, G, P, px, py, w);
+        adj_open<R>(P, onW, onE, onS, onN, lout, w,
+                    [&]() { return PN ? R(med[size_t(y) * G.pitch + x]) : P.phi; });
         if (wall) {
             adj_hand_over<R>(w, [&](int i, R v) { handoff[i][me] = v; });
             const bool okx_m = !onW, okx_p = !onE, oky_m = !onS, oky_p = !onN;
@@ -450,8 +456,16 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
 // wall in.  The forward states of the steps come from the recomputed segment; hand-offs are
 // indexed by the wall nodes' place along the region's sides; the gradient's sums are kept in LDS
 // and take each step's terms in the order of single steps.
+//
+// AHEAD: while every tile has a compute unit of its own, a work-item keeps its node for all steps,
+// with the medium and the place worked out once, and loads the next step's forward state before
+// the step's arithmetic; the registers this takes (142 against 122) are free there.  Beyond, where
+// two work-groups share a compute unit, they cost one of the two its place, and the nodes are
+// dealt anew in each step.  lbm_grad, FP32, us per step, dealt / AHEAD: 48^2 6.70 / 5.72, 128^2
+// 6.33 / 5.65, 256^2 7.02 / 6.58 (256 tiles); 250 x 300 (304 tiles) 8.6 / 10.3, 330^2 10.4 / 11.4.
 constexpr int kAdjRegion = kAdjSide + 2 * (kAdjSteps - 1) + 2;   // region side at most
 constexpr int kAdjTileThreads = (kAdjRegion * kAdjRegion + 63) / 64 * 64;
+constexpr int kAdjAheadWGs = 256;   // tiles up to which AHEAD is taken: one per compute unit
 constexpr int kAdjRow = kAdjRegion + 2;   // row of the adjoint in LDS: a margin on each side takes
                                           // the slots of the region's edge nodes that nobody reads
 
@@ -466,7 +480,7 @@ constexpr size_t adjoint_tile_lds() {
            14 * size_t(kAdjRow) * kAdjRow * sizeof(S);
 }
 
-template <typename S, typename R, bool PN>
+template <typename S, typename R, bool PN, bool AHEAD>
 __global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
     AdjStates<S> X, const S* __restrict__ lam_in, S* __restrict__ lam_out,
     const S* __restrict__ med, double* __restrict__ gphi, double* __restrict__ gK, Geo G,
@@ -488,30 +502,75 @@ __global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
     if (G.wallN && ry1 >= G.ny - 1) { ry1 = G.ny; openN = 0; }
     const int RW = rx1 - rx0, RH = ry1 - ry0;   // at most W each
 
-    // slots whose owner lies beyond a wall are never written and read as zero
-    for (int k = threadIdx.x; k < 14 * L; k += kAdjTileThreads) lam[k] = S(0);
-
     const int me = threadIdx.x;
-    const float fme = float(me) + 0.5f;
-#pragma unroll 1
-    for (int s = 1; s <= K; ++s) {
-        // the active nodes, dealt row by row as in the forward tile
+    struct Place {
+        int lx, ly, x, y, px, py, c, tn;   // in the region, the grid, pulled at, in LDS
+        bool onW, onE, onS, onN, wall, inner, mine;
+    };
+    // the active nodes of step s, dealt row by row as in the forward tile
+    auto deal = [&](int s) {
         const int ax = openW ? s - 1 : 0, ay = openS ? s - 1 : 0;
         const int aw = RW - (openE ? s - 1 : 0) - ax, ah = RH - (openN ? s - 1 : 0) - ay;
-        const int row = int(fme * __builtin_amdgcn_rcpf(float(aw)));
-        const bool mine = row < ah;
-        const int lx = ax + me - row * aw, ly = ay + row;
-        const int ux = rx0 + lx, uy = ry0 + ly;   // unwrapped
-        int x = ux, y = uy;
-        if (!G.wallW) { x %= G.nx; x += x < 0 ? G.nx : 0; }
-        if (!G.wallS) { y %= G.ny; y += y < 0 ? G.ny : 0; }
-        const bool onW = G.wallW && x == 0, onE = G.wallE && x == G.nx - 1;
-        const bool onS = G.wallS && y == 0, onN = G.wallN && y == G.ny - 1;
-        const bool wall = onW || onE || onS || onN;
-        const bool inner = mine && ux >= x0 && ux < x1 && uy >= y0 && uy < y1;
+        const int row = int((float(me) + 0.5f) * __builtin_amdgcn_rcpf(float(aw)));
+        Place q;
+        q.mine = row < ah;
+        q.lx = ax + me - row * aw;
+        q.ly = ay + row;
+        const int ux = rx0 + q.lx, uy = ry0 + q.ly;   // unwrapped
+        q.x = ux;
+        q.y = uy;
+        if (!G.wallW) { q.x %= G.nx; q.x += q.x < 0 ? G.nx : 0; }
+        if (!G.wallS) { q.y %= G.ny; q.y += q.y < 0 ? G.ny : 0; }
+        q.onW = G.wallW && q.x == 0;
+        q.onE = G.wallE && q.x == G.nx - 1;
+        q.onS = G.wallS && q.y == 0;
+        q.onN = G.wallN && q.y == G.ny - 1;
+        q.wall = q.onW || q.onE || q.onS || q.onN;
+        q.px = q.x + (q.onW ? 1 : 0) - (q.onE ? 1 : 0);
+        q.py = q.y + (q.onS ? 1 : 0) - (q.onN ? 1 : 0);
+        q.inner = q.mine && ux >= x0 && ux < x1 && uy >= y0 && uy < y1;
+        q.c = (q.ly + 1) * LW + q.lx + 1;
+        q.tn = (uy - y0) * TS + (ux - x0);
+        return q;
+    };
+
+    // AHEAD: this work-item's node, the same for all steps, with its medium and the next step's
+    // forward state
+    Place kept;
+    AdjNode<R> next;
+    R own_phi = P.phi;
+    if constexpr (AHEAD) {
+        kept = deal(1);
+        if (kept.mine) {
+            pull<R, S>(X.X[0], G, kept.px, kept.py, next.f, next.g);
+            adj_medium<S, R, PN>(med, G, P, kept.px, kept.py, next);
+            if (PN && kept.wall) own_phi = R(med[size_t(kept.y) * G.pitch + kept.x]);
+        }
+    }
+
+    // slots whose owner lies beyond a wall are never written and read as zero
+    for (int k = me; k < 14 * L; k += kAdjTileThreads) lam[k] = S(0);
+
+#pragma unroll 1
+    for (int s = 1; s <= K; ++s) {
+        if constexpr (AHEAD) {
+            if (s > 1) {
+                const int ax = openW ? s - 1 : 0, ay = openS ? s - 1 : 0;
+                const int aw = RW - (openE ? s - 1 : 0) - ax, ah = RH - (openN ? s - 1 : 0) - ay;
+                kept.mine = kept.mine && unsigned(kept.lx - ax) < unsigned(aw) &&
+                            unsigned(kept.ly - ay) < unsigned(ah);
+            }
+            // hide that these do not change, so that the offsets derived from them are worked out
+            // where they are used instead of being kept in registers through the loop
+            asm volatile("" : "+v"(kept.x), "+v"(kept.y), "+v"(kept.px), "+v"(kept.py),
+                         "+v"(kept.c), "+v"(kept.tn), "+v"(kept.lx), "+v"(kept.ly));
+        }
+        const Place q = AHEAD ? kept : deal(s);
+        const int lx = q.lx, ly = q.ly, x = q.x, y = q.y, px = q.px, py = q.py, c = q.c, tn = q.tn;
+        const bool onW = q.onW, onE = q.onE, onS = q.onS, onN = q.onN;
+        const bool wall = q.wall, inner = q.inner, mine = q.mine;
         const unsigned on = unsigned(y) * unsigned(G.pitch) + unsigned(x);
         const unsigned og = on * unsigned(sizeof(double));
-        const int c = (ly + 1) * LW + lx + 1, tn = (uy - y0) * TS + (ux - x0);
         double gphi0 = 0, gK0 = 0;
         AdjNode<R> w;
         if (mine) {
@@ -532,7 +591,22 @@ __global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
 #pragma unroll
                 for (int i = 0; i < 14; ++i) lout[i] = R(lam[i * L + c]);
             }
-            adj_open<S, R, PN>(X.X[s - 1], med, G, P, x, y, onW, onE, onS, onN, lout, w);
+            if constexpr (AHEAD) {
+                w.phi = next.phi;
+                w.K = next.K;
+                w.md = next.md;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) w.f[i] = next.f[i];
+#pragma unroll
+                for (int i = 0; i < 5; ++i) w.g[i] = next.g[i];
+                if (s < K) pull<R, S>(X.X[s], G, px, py, next.f, next.g);
+            } else {
+                pull<R, S>(X.X[s - 1], G, px, py, w.f, w.g);
+                adj_medium<S, R, PN>(med, G, P, px, py, w);
+            }
+            adj_open<R>(P, onW, onE, onS, onN, lout, w, [&]() {
+                return AHEAD || !PN ? own_phi : R(med[size_t(y) * G.pitch + x]);
+            });
             if (wall) {
                 const int j = onW ? ly : onE ? W + ly : onS ? 2 * W + lx : 3 * W + lx;
                 adj_hand_over<R>(w, [&](int i, R v) { hand[i * 4 * W + j] = v; });
@@ -670,7 +744,7 @@ hipError_t launch_adjoint_step(const void* state, const void* lam_in, void* lam_
 }
 
 // Where kAdjSteps backward steps per launch beat one (us per step of lbm_grad, FP32, one / three:
-// 64^2 9.2 / 7.3, 128^2 9.4 / 7.0, 256^2 8.8 / 7.6, 320^2 10.9 / 10.4, 384^2 13.8 / 14.4, 1024^2
+// 64^2 9.2 / 5.7, 128^2 9.4 / 5.7, 256^2 8.8 / 6.6, 320^2 10.9 / 10.0, 384^2 13.8 / 14.4, 1024^2
 // 62.6 / 69.3): up to about 320^2, where the launch costs more than the halo's redundant work
 // (1.27 times the tile's nodes).  With FP64 arithmetic a step is 1,100 instructions of a register-
 // and scalar-bound kernel, and one per launch is as fast or faster from 48^2 on (64^2 9.8 / 9.6,
@@ -691,12 +765,17 @@ hipError_t launch_adjoint_tiles(const void* const states[kAdjSteps], const void*
         const int nwg = tiles_x * ((G.ny + kAdjSide - 1) / kAdjSide);
         constexpr size_t lds = adjoint_tile_lds<S, R>();
         static_assert(lds <= 160 * 1024, "adjoint region exceeds the LDS of a CU");
-        if (med)
-            adjoint_tile_kernel<S, R, true><<<nwg, kAdjTileThreads, lds, s>>>(
-                X, (const S*)lam_in, (S*)lam_out, (const S*)med, gphi, gK, G, P, tiles_x);
+        auto go = [&](auto pn, auto ahead) {
+            adjoint_tile_kernel<S, R, decltype(pn)::value, decltype(ahead)::value>
+                <<<nwg, kAdjTileThreads, lds, s>>>(X, (const S*)lam_in, (S*)lam_out,
+                                                   (const S*)med, gphi, gK, G, P, tiles_x);
+        };
+        using Yes = std::true_type;
+        using No = std::false_type;
+        if (nwg <= kAdjAheadWGs)   // see adjoint_tile_kernel
+            med ? go(Yes{}, Yes{}) : go(No{}, Yes{});
         else
-            adjoint_tile_kernel<S, R, false><<<nwg, kAdjTileThreads, lds, s>>>(
-                X, (const S*)lam_in, (S*)lam_out, nullptr, gphi, gK, G, P, tiles_x);
+            med ? go(Yes{}, No{}) : go(No{}, No{});
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;
