@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
 }
 
 // kAdjSteps backward steps per launch, bitwise as that many launches of adjoint_step_kernel would
-// take them (FP32): the adjoint of a tile of kAdjSide^2 nodes and its halo stays in LDS from step
+// take them: the adjoint of a tile of kAdjSide^2 nodes and its halo stays in LDS from step
 // to step.  On a small grid a backward step is latency, not work: at 256^2 its kernel took 6.8 us
 // (7.8 with the gap to the next), of which the arithmetic of one wavefront per SIMD is a quarter;
 // the launch and the round trip of the adjoint through memory are paid once per launch here.  The dataflow is the forward tile's with the arrows turned round: node x writes slot
@@ -743,26 +743,31 @@ hipError_t launch_adjoint_step(const void* state, const void* lam_in, void* lam_
     return hipGetLastError();
 }
 
+static int adjoint_tiles(const Geo& G) {
+    return ((G.nx + kAdjSide - 1) / kAdjSide) * ((G.ny + kAdjSide - 1) / kAdjSide);
+}
+
 // Where kAdjSteps backward steps per launch beat one (us per step of lbm_grad, FP32, one / three:
 // 64^2 9.2 / 5.7, 128^2 9.4 / 5.7, 256^2 8.8 / 6.6, 320^2 10.9 / 10.0, 384^2 13.8 / 14.4, 1024^2
 // 62.6 / 69.3): up to about 320^2, where the launch costs more than the halo's redundant work
-// (1.27 times the tile's nodes).  With FP64 arithmetic a step is 1,100 instructions of a register-
-// and scalar-bound kernel, and one per launch is as fast or faster from 48^2 on (64^2 9.8 / 9.6,
-// 256^2 11.5 / 11.8; FP32 storage 8.9 / 9.2, 9.4 / 10.7), so there is no such form.
+// (1.27 times the tile's nodes).  FP64 takes them where the tiles are AHEAD (48^2 9.6 / 8.6, 128^2
+// 9.4 / 8.9, 256^2 11.4 / 10.8); beyond, and with FP64 arithmetic on FP32 storage (64^2 8.4 / 9.4,
+// 256^2 9.1 / 12.1), a step of 1,100 instructions in a register-bound kernel is faster alone.
 template <typename S, typename R>
 bool adjoint_by_tiles(const Geo& G) {
-    return sizeof(R) == 4 && (long long)G.nx * G.ny <= 110000;
+    if (sizeof(R) == 4) return (long long)G.nx * G.ny <= 110000;
+    return sizeof(S) == 8 && adjoint_tiles(G) <= kAdjAheadWGs;
 }
 
 template <typename S, typename R>
 hipError_t launch_adjoint_tiles(const void* const states[kAdjSteps], const void* lam_in,
                                 void* lam_out, const void* med, double* gphi, double* gK,
                                 const Geo& G, const Phys<R>& P, hipStream_t s) {
-    if constexpr (sizeof(R) == 4) {
+    if constexpr (sizeof(S) == sizeof(R)) {
         AdjStates<S> X;
         for (int k = 0; k < kAdjSteps; ++k) X.X[k] = (const S*)states[k];
         const int tiles_x = (G.nx + kAdjSide - 1) / kAdjSide;
-        const int nwg = tiles_x * ((G.ny + kAdjSide - 1) / kAdjSide);
+        const int nwg = adjoint_tiles(G);
         constexpr size_t lds = adjoint_tile_lds<S, R>();
         static_assert(lds <= 160 * 1024, "adjoint region exceeds the LDS of a CU");
         auto go = [&](auto pn, auto ahead) {
@@ -772,10 +777,11 @@ hipError_t launch_adjoint_tiles(const void* const states[kAdjSteps], const void*
         };
         using Yes = std::true_type;
         using No = std::false_type;
-        if (nwg <= kAdjAheadWGs)   // see adjoint_tile_kernel
+        if (sizeof(R) == 8 || nwg <= kAdjAheadWGs) {
             med ? go(Yes{}, Yes{}) : go(No{}, Yes{});
-        else
-            med ? go(Yes{}, No{}) : go(No{}, No{});
+        } else {
+            if constexpr (sizeof(R) == 4) med ? go(Yes{}, No{}) : go(No{}, No{});
+        }
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;

@@ -105,7 +105,8 @@ template <typename S, typename R>
 hipError_t launch_adjoint_step(const void* state, const void* lam_in, void* lam_out,
                                const void* med, double* gphi, double* gK, const Geo& G,
                                const Phys<R>& P, hipStream_t s);
-// Whether kAdjSteps backward steps per launch are faster than one (FP32, small grids)
+// Whether kAdjSteps backward steps per launch are faster than one (small grids, not FP64 arithmetic
+// on FP32 storage)
 template <typename S, typename R>
 bool adjoint_by_tiles(const Geo& G);
 // kAdjSteps backward steps in one launch, each tile of kAdjSide^2 nodes in LDS; states: X^n,

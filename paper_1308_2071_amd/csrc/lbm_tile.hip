@@ -83,13 +83,13 @@ int default_steps(const Geo& G, bool per_node_medium) {
 }
 
 // Steps per launch of the adjoint's recompute, which runs beside the backward sweep: the default,
-// except with FP64 arithmetic up to 256^2, where one backward step per launch sets the pace and a
-// tile's work-group holds up the sweep's longer than a single step's does (lbm_grad, us per step,
-// one / several recomputed per launch: FP64 96^2 9.5 / 9.7, 256^2 11.7 / 11.7; FP32 storage 128^2
-// 8.3 / 8.8, 256^2 9.1 / 9.9; FP64 320^2, where several pay, 17.2 / 15.8).
+// except for FP64 arithmetic on FP32 storage up to 256^2, where one backward step per launch sets
+// the pace and a tile's work-group holds up the sweep's longer than a single step's does (lbm_grad,
+// us per step, one / several recomputed per launch: 128^2 8.3 / 8.8, 256^2 9.1 / 9.9; FP64, whose
+// sweep takes tiles there, 64^2 9.2 / 8.6, 256^2 13.1 / 10.8).
 template <typename S, typename R>
 int recompute_steps(const Geo& G, bool per_node_medium) {
-    if (sizeof(R) == 8 && (long long)G.nx * G.ny <= 256LL * 256) return 1;
+    if (sizeof(S) == 4 && sizeof(R) == 8 && (long long)G.nx * G.ny <= 256LL * 256) return 1;
     return default_steps<S, R>(G, per_node_medium);
 }
 
