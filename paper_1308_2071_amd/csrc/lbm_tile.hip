@@ -47,26 +47,29 @@ __global__ __launch_bounds__(F::NT, (F::template waves<R>())) void tile_trace_ke
 // and shrinks with the tile, the launches and the bytes per step fall with the steps.  Measured,
 // us per step on porous cavities, uniform / per-node medium:
 //                          8 x 8, 8    16 x 16, 4  28 x 12, 3  28 x 28, 3  30 x 14, 2
-//   FP32          128^2    1.46 1.51   1.95 1.94   2.13 2.17   3.27 3.37   2.49 2.58
-//                 192^2    2.11 2.21   1.97 1.97   2.14 2.20   3.35 3.38   2.57 2.64
-//                 512^2    8.22 8.50   4.11 4.26   4.54 4.56   5.27 5.43   4.56 4.69
-//                 1024^2   29.5 30.7   11.8 12.4   11.3 12.0   12.1 12.5   12.2 12.7
-//                 2048^2   114  119    47.0 50.1   45.2 49.2   43.7 46.0   54.6 58.4
-//                 4096^2   450  472    188  201    182  198    163  178    224  242
+//   FP32          128^2    1.46 1.51   1.95 1.94   1.96 2.01   3.27 3.37   2.49 2.58
+//                 192^2    2.11 2.21   1.97 1.97   1.96 2.02   3.35 3.38   2.57 2.64
+//                 512^2    8.22 8.50   4.11 4.26   4.24 4.48   5.27 5.43   4.56 4.69
+//                 1024^2   29.5 30.7   11.8 12.4   10.6 12.2   12.1 12.5   12.2 12.7
+//                 2048^2   114  119    47.0 50.1   45.2 49.2   40.0 45.3   54.6 58.4
+//                 4096^2   450  472    188  201    182  198    150  167    224  242
 //   FP64          128^2    1.85 1.93   2.67 2.80   2.91 3.18               3.42 3.70
-//                 256^2    4.58 4.86   2.85 2.98   3.14 3.43               3.73 4.08
-//                 517 x 389 11.8 12.5  6.43 6.86   6.25 6.77               6.20 6.66
-//                 1024^2   53.9 57.6   21.8 23.4   20.0 21.6               21.3 24.3
-//                 4096^2   829  921    325  373    302  368                408  444
+//                 256^2    4.58 4.86   2.85 2.98   3.1  3.4                3.73 4.08
+//                 517 x 389 11.8 12.5  6.43 6.86   5.95 6.36               6.20 6.66
+//                 1024^2   53.9 57.6   21.8 23.4   18.5 21.8               21.3 24.3
+//                 4096^2   829  921    325  373    292  368                408  444
 //   FP32 storage, 128^2    1.78 2.00   2.53 2.71   2.94 3.11               3.25 3.53
 //   FP64          256^2    4.54 4.96   2.54 2.74   2.97 3.18               3.31 3.62
 //   arithmetic    517 x 389 12.2 12.9  6.10 6.48   5.80 6.16               4.99 5.48
 //                 1024^2   57.8 60.5   21.6 22.9   19.0 20.2               16.0 19.4
 //                 4096^2   885  953    302  328    265  297                244  311
-// One step per launch takes 2 to 3 times as long on the smallest of these and 1.1 to 1.9 times on
-// the largest.  Per-node media from 1024^2 to 1536^2 in FP32, and from 4096^2 in FP64, keep two
-// steps per launch, which lbm_step_shape has long reported for these grids (three would run
-// 6 to 20 % faster).
+// (28 x 28 below 2048^2 and 28 x 12 from there in FP32: measured with the nodes dealt anew in each
+// step, which takes 3 to 6 % longer.)  One step per launch takes 2 to 3 times as long on the
+// smallest of these and 1.1 to 1.9 times on the largest.  FP32 goes from four steps to three between
+// 512^2 and 600 x 520 (uniform 4.65 / 4.42, per-node 4.90 / 4.77; 760 x 520 5.72 / 5.33, 5.96 /
+// 5.65; 800^2 7.70 / 7.36, 8.5 / 8.05).  Per-node media from 1024^2 to 1536^2 in
+// FP32, and from 4096^2 in FP64, keep two steps per launch, which lbm_step_shape has long reported
+// for these grids (three would run 6 to 20 % faster).
 constexpr long long kTinyTileMaxNodes = 128LL * 128;
 
 template <typename S, typename R>
@@ -74,7 +77,7 @@ int default_steps(const Geo& G, bool per_node_medium) {
     const long long n = (long long)G.nx * G.ny;
     if (n <= kTinyTileMaxNodes) return kTinyTileSteps;
     if (sizeof(R) == 4) {
-        if (n <= 700000) return kTileSteps;
+        if (n <= 300000) return kTileSteps;
         return per_node_medium && n >= 1024LL * 1024 && n <= 1536LL * 1536 ? 2 : 3;
     }
     if (sizeof(S) == 4) return n <= 110000 ? kTileSteps : 2;
