@@ -6,7 +6,7 @@ phi ~ U[0.3, 0.9] (seeded), Kozeny-Carman permeability with mean Da = 1e-3, Ra =
 FP32 storage, inputs resident in HBM before timing.  A step is one full time step of every node
 (pull streaming, wall reconstruction, macroscopics, flow and thermal MRT collision), in FP32
 arithmetic (--dtype fp32, the default) or FP64 arithmetic on the same FP32 storage
-(--dtype fp32_f64).  The library's default time loop is timed: on this grid it fuses three steps
+(--dtype fp32_f64).  The library's default time loop is timed: on this grid it takes three steps
 per launch in FP32, two with FP64 arithmetic.  Extra legs: one and two steps per launch, the
 other arithmetic type, the AA layout,
 the batched form, the adjoint, the 64^2 FP64 cavity, and the 256^2 cavity in every precision
