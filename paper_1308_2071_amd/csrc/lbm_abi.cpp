@@ -699,7 +699,10 @@ lbm_status ensure_batch_graph(lbm_ctx* c, int start) {
     return LBM_OK;
 }
 
-// Cache key: device architecture, dtype and the list of cavity shapes.
+// Cache key: device architecture, dtype, and a hash of the cavity shapes and of kBatchTiles, so that
+// a line tuned over another set of tiles, whose last two numbers mean other shapes, is not found
+// and the batch is tuned anew (read as a tile, the winner of the strips that came before these tiles
+// took the 64-cavity workload 88 us per step, tuned anew it takes 54).
 std::string batch_key(const lbm_ctx* c) {
     hipDeviceProp_t prop;
     int dev = 0;
@@ -720,6 +723,8 @@ std::string batch_key(const lbm_ctx* c) {
         mix(uint64_t(G.nx));
         mix(uint64_t(G.ny));
     }
+    for (const BatchTile& f : kBatchTiles)
+        for (int v : {f.cols, f.rows, f.steps, f.code}) mix(uint64_t(v));
     char buf[128];
     snprintf(buf, sizeof buf, "v3|%s|%s|%016llx", arch.c_str(),
              c->p.dtype == LBM_FP64 ? "fp64" : c->p.dtype == LBM_FP32_F64 ? "fp32_f64" : "fp32",
@@ -728,8 +733,8 @@ std::string batch_key(const lbm_ctx* c) {
 }
 
 // A cache line: key, rows per tile, 64-node segments per work-item, work-groups (0: one tile
-// per work-group), rows per tile of the several-step form (0: one step per launch) and how many of
-// its tiles' regions make 64 columns.
+// per work-group), rows per tile of the several-step form (0: one step per launch) and the tile's
+// code (see BatchTile).
 bool cache_lookup(const char* path, const std::string& key, int* wg, int* npt, int* nwg,
                   int* tb_rows, int* tb_code) {
     FILE* f = std::fopen(path, "r");
