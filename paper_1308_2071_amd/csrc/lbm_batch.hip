@@ -141,7 +141,12 @@ static hipError_t launch_two_steps(const void* src, void* dst, const BatchTable<
 template <typename S, typename R>
 hipError_t launch_batch_tiles(const void* src, void* dst, const BatchTable<R>& T,
                               const BatchTile& f, hipStream_t s) {
-    if (f.steps == 2) {
+    if (f.steps == 2 && f.cols == 28) {          // the remainder of three steps
+        if (f.rows == 12) return launch_tiles<S, R, 28, 12, 2>(src, dst, T, s);
+        if (f.rows == 28) return launch_tiles<S, R, 28, 28, 2>(src, dst, T, s);
+    } else if (f.steps == 2 && f.cols == 16) {   // and of four
+        if (f.rows == 16) return launch_tiles<S, R, 16, 16, 2>(src, dst, T, s);
+    } else if (f.steps == 2) {
         switch (f.rows) {
             case 2: return launch_two_steps<S, R, 2>(src, dst, T, f.cols, s);
             case 3: return launch_two_steps<S, R, 3>(src, dst, T, f.cols, s);

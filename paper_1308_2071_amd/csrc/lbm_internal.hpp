@@ -139,7 +139,8 @@ struct BatchTable {
     int ntiles;
 };
 
-// f.steps steps per launch for every cavity of a batch, in tiles f (one of kBatchTiles):
+// f.steps steps per launch for every cavity of a batch, in tiles f: one of kBatchTiles, or one of
+// those with three or four steps for two steps.
 // T.tile_cav maps each of the T.ntiles tiles to its cavity, whose tile0 is its first tile and
 // tiles_x its tiles along x.
 template <typename S, typename R>
