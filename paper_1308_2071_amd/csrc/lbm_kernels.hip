@@ -370,24 +370,23 @@ __global__ __launch_bounds__(256) void batch_observe_results_kernel(
 }
 
 // Stream function: u_x (Eq. (21)) integrated along y with the trapezoid rule in FP64,
-// psi(x, 0) = 0.  A work-group owns kPsiCols columns and takes kPsiRows rows at a time: a
-// work-item sums kPsiPer consecutive rows of one column, the sums of the kPsiSlots work-items of
+// psi(x, 0) = 0.  A work-group owns COLS columns and takes kPsiPer * SLOTS rows at a time: a
+// work-item sums kPsiPer consecutive rows of one column, the sums of the SLOTS work-items of
 // a column are scanned in LDS, and the column's total carries over to the next rows.  (One
 // work-item per column, row after row, is a chain of ny dependent gathers: 97 us at 301 x 199
 // against 10.5 us this way.)
-constexpr int kPsiCols = 16, kPsiPer = 4, kPsiSlots = 1024 / kPsiCols;
-constexpr int kPsiRows = kPsiPer * kPsiSlots;
+constexpr int kPsiPer = 4;
 
-template <typename S, typename R, bool PN, int L>
-__global__ __launch_bounds__(kPsiCols * kPsiSlots) void stream_function_kernel(
+template <typename S, typename R, bool PN, int L, int COLS, int SLOTS>
+__global__ __launch_bounds__(COLS* SLOTS) void stream_function_kernel(
     const S* __restrict__ src, const S* __restrict__ med, Geo G, Phys<R> P,
     S* __restrict__ psi) {
-    __shared__ double edge[kPsiSlots][kPsiCols];   // u of each slot's last row
-    __shared__ double sums[2][kPsiSlots][kPsiCols];
-    const int col = threadIdx.x % kPsiCols, slot = threadIdx.x / kPsiCols;
-    const int x = blockIdx.x * kPsiCols + col;
+    __shared__ double edge[SLOTS][COLS];   // u of each slot's last row
+    __shared__ double sums[2][SLOTS][COLS];
+    const int col = threadIdx.x % COLS, slot = threadIdx.x / COLS;
+    const int x = blockIdx.x * COLS + col;
     double carry = 0.0, before = 0.0;   // psi and u at the last row of the rows done so far
-    for (int base = 0; base < G.ny; base += kPsiRows) {
+    for (int base = 0; base < G.ny; base += kPsiPer * SLOTS) {
         const int y0 = base + slot * kPsiPer;
         double u[kPsiPer];
 #pragma unroll
@@ -404,7 +403,7 @@ __global__ __launch_bounds__(kPsiCols * kPsiSlots) void stream_function_kernel(
         edge[slot][col] = u[kPsiPer - 1];
         __syncthreads();
         const double prev = slot > 0 ? edge[slot - 1][col] : before;
-        before = edge[kPsiSlots - 1][col];
+        before = edge[SLOTS - 1][col];
         // increments up to each of this work-item's rows (none into row 0)
         double inc[kPsiPer];
         double acc = y0 > 0 ? 0.5 * (prev + u[0]) : 0.0;
@@ -417,7 +416,7 @@ __global__ __launch_bounds__(kPsiCols * kPsiSlots) void stream_function_kernel(
         int cur = 0;
         sums[0][slot][col] = acc;
         __syncthreads();
-        for (int d = 1; d < kPsiSlots; d <<= 1) {
+        for (int d = 1; d < SLOTS; d <<= 1) {
             double t = sums[cur][slot][col];
             if (slot >= d) t += sums[cur][slot - d][col];
             sums[1 - cur][slot][col] = t;
@@ -425,7 +424,7 @@ __global__ __launch_bounds__(kPsiCols * kPsiSlots) void stream_function_kernel(
             __syncthreads();
         }
         const double start = carry + (slot > 0 ? sums[cur][slot - 1][col] : 0.0);
-        carry += sums[cur][kPsiSlots - 1][col];
+        carry += sums[cur][SLOTS - 1][col];
 #pragma unroll
         for (int j = 0; j < kPsiPer; ++j)
             if (x < G.nx && y0 + j < G.ny) psi[(y0 + j) * G.nx + x] = S(start + inc[j]);
@@ -573,13 +572,26 @@ hipError_t launch_batch_observe(const void* src, const BatchTable<R>& T, long lo
 template <typename S, typename R, int L>
 static hipError_t stream_function_l(const void* src, const void* med, const Geo& G,
                                     const Phys<R>& P, void* psi, hipStream_t s) {
-    const int nb = (G.nx + kPsiCols - 1) / kPsiCols;
-    if (med)
-        stream_function_kernel<S, R, true, L><<<nb, kPsiCols * kPsiSlots, 0, s>>>(
-            (const S*)src, (const S*)med, G, P, (S*)psi);
+    auto go = [&](auto cols, auto slots) {
+        constexpr int C = decltype(cols)::value, N = decltype(slots)::value;
+        const int nb = (G.nx + C - 1) / C;
+        if (med)
+            stream_function_kernel<S, R, true, L, C, N><<<nb, C * N, 0, s>>>(
+                (const S*)src, (const S*)med, G, P, (S*)psi);
+        else
+            stream_function_kernel<S, R, false, L, C, N><<<nb, C * N, 0, s>>>(
+                (const S*)src, nullptr, G, P, (S*)psi);
+    };
+    // Work-groups of 16 columns and 256 rows at a time; on wide grids, whose columns alone fill the
+    // GPU, of 64 columns and 32 rows, which read whole cache lines and leave no work-item without a
+    // row where there are few (us, 16 x 256 / 64 x 32: FP32 8192 x 40 23.4 / 19.3, 20000 x 5 25.7 /
+    // 15.7, 20000 x 200 104 / 65, 50000 x 400 443 / 304, 100000 x 5 88 / 20; FP64 20000 x 100 70 / 62,
+    // 50000 x 400 577 / 582; where the columns do not suffice: FP64 8192 x 1000 233 / 270, FP32
+    // 4096 x 1000 101 / 143).
+    if (G.nx >= 32768 || (G.nx >= 8192 && G.ny <= 256))
+        go(std::integral_constant<int, 64>{}, std::integral_constant<int, 8>{});
     else
-        stream_function_kernel<S, R, false, L><<<nb, kPsiCols * kPsiSlots, 0, s>>>(
-            (const S*)src, nullptr, G, P, (S*)psi);
+        go(std::integral_constant<int, 16>{}, std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 
