@@ -555,18 +555,29 @@ hipError_t launch_observe(const void* src, const void* med, const Geo& G, const 
     }
 }
 
+// Cavities per launch of the batch's observables: the cavity is the grid's y index, of which a device
+// takes 65,536 at most, while a batch holds up to about 130,000 cavities of the smallest size.
+constexpr int kBatchObsCavities = 32768;
+
 template <typename S, typename R>
 hipError_t launch_batch_observe(const void* src, const BatchTable<R>& T, long long largest,
                                 double* part, double* out, hipStream_t s) {
     constexpr int per = kObsParts * kBatchObsWG + 2 * kNuWG;
     int nwg = 0, threads = 0;
     observe_shape(largest, kBatchObsWG, &nwg, &threads);
-    batch_observe_kernel<S, R><<<dim3(nwg + kNuWG, T.ncav), threads, 0, s>>>(
-        (const S*)src, T.cav, T.phys, part, per, nwg);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    batch_observe_results_kernel<<<T.ncav, 256, 0, s>>>(part, T.cav, per, nwg, out);
-    return hipGetLastError();
+    for (int c = 0; c < T.ncav; c += kBatchObsCavities) {
+        const int n = min(T.ncav - c, kBatchObsCavities);
+        double* const mine = part + size_t(c) * per;
+        batch_observe_kernel<S, R><<<dim3(nwg + kNuWG, n), threads, 0, s>>>(
+            (const S*)src, T.cav + c, T.phys + c, mine, per, nwg);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        batch_observe_results_kernel<<<n, 256, 0, s>>>(mine, T.cav + c, per, nwg,
+                                                       out + size_t(kObsOut) * c);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename S, typename R, int L>
