@@ -1527,7 +1527,7 @@ lbm_status lbm_step_shape(const lbm_ctx* c, int32_t* out) {
     out[0] = k;
     out[1] = c->p.layout;
     out[2] = 0;
-    out[3] = (c->G.nx + kTileX - 1) / kTileX * c->G.ny;
+    out[3] = one_step_groups(c->G, storage_bytes(c->p.dtype), c->p.layout == LBM_LAYOUT_AA);
     if (k > 1)
         (void)with_types(c->p.dtype, [&](auto st, auto rt) {
             LBM_TYPES(st, rt)

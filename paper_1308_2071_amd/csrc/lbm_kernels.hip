@@ -469,11 +469,19 @@ static bool aa_in_tiles(const Geo& G, size_t elem_bytes) {
     return state_bytes(G, elem_bytes) <= size_t(256) << 20;
 }
 
+int one_step_groups(const Geo& G, size_t elem_bytes, bool aa) {
+    if (aa && aa_in_tiles(G, elem_bytes)) {
+        const WallTiles T = wall_tiles(G, kAATX, kAATY);
+        return T.nx_tiles * T.ny_tiles;
+    }
+    return (G.nx + kTileX - 1) / kTileX * G.ny;
+}
+
 template <typename S, typename R>
 hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G,
                        const Phys<R>& P, hipStream_t s) {
     const int tiles_x = (G.nx + kTileX - 1) / kTileX;
-    const int nwg = tiles_x * G.ny;
+    const int nwg = one_step_groups(G, sizeof(S), false);
     const int by_xcd = state_bytes(G, sizeof(S)) <= size_t(32) << 20 ? 1 : 0;
     if (med)
         step_kernel<S, R, true><<<nwg, kTileX, 0, s>>>((const S*)src, (S*)dst, (const S*)med, G,
@@ -486,16 +494,15 @@ hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G
 
 template <typename S, typename R, int L>
 static hipError_t aa_launch(S* b, const S* m, const Geo& G, const Phys<R>& P, hipStream_t s) {
+    const int nwg = one_step_groups(G, sizeof(S), true);
     if (aa_in_tiles(G, sizeof(S))) {
         const WallTiles T = wall_tiles(G, kAATX, kAATY);
-        const int nwg = T.nx_tiles * T.ny_tiles;
         if (m)
             aa_tile_step_kernel<S, R, true, L><<<nwg, kAATX * kAATY, 0, s>>>(b, m, G, P, T);
         else
             aa_tile_step_kernel<S, R, false, L><<<nwg, kAATX * kAATY, 0, s>>>(b, m, G, P, T);
     } else {
         const int tiles_x = (G.nx + kTileX - 1) / kTileX;
-        const int nwg = tiles_x * G.ny;
         if (m)
             aa_step_kernel<S, R, true, L><<<nwg, kTileX, 0, s>>>(b, m, G, P, tiles_x);
         else
