@@ -235,8 +235,6 @@ struct AdjNode {
     R f[9], g[5], af[9], ag[5], phi, K;
     Med<R> md;
     MacAdj<R> A;
-    MacAdj<R> H;    // wall node: what its inward neighbour's macroscopics receive
-    R lphib;        // wall node: its dJ/dphi
 };
 
 // Byte offsets, within a plane, of the node (x, y) and of the slots it owns: o[i] that of slot
@@ -284,10 +282,15 @@ __device__ __forceinline__ void adj_medium(const S* __restrict__ med, const Geo&
 // (px, py), with w's medium there; own_phi(): phi of a wall node itself; lout: adjoint of X^{n+1}
 // in the node's own 14 slots.  A fluid node reverses its own collision.  A wall node runs the same
 // macroscopics and collision VJP on its own reconstructed state (so both kinds of node stay in
-// step), then reverses the reconstruction.
-template <typename R, typename OwnPhi>
+// step), then reverses the reconstruction and calls at_wall(H, lphib): what its inward neighbour's
+// macroscopics receive, and its own dJ/dphi.  Whatever a wall node does before the barrier goes in
+// at_wall: in a branch of its own after this one it kept H and more alive for every node (vector
+// registers of adjoint_step_kernel FP32 101 to 81, FP64 187 to 147, the wavefronts per SIMD 4 to 5
+// and 2 to 3).
+template <typename R, typename OwnPhi, typename AtWall>
 __device__ __forceinline__ void adj_open(const Phys<R>& P, bool onW, bool onE, bool onS, bool onN,
-                                         const R lout[14], AdjNode<R>& w, OwnPhi&& own_phi) {
+                                         const R lout[14], AdjNode<R>& w, OwnPhi&& own_phi,
+                                         AtWall&& at_wall) {
     const bool wall = onW || onE || onS || onN;
     R (&f)[9] = w.f;
     R (&g)[5] = w.g;
@@ -317,27 +320,28 @@ __device__ __forceinline__ void adj_open(const Phys<R>& P, bool onW, bool onE, b
         // at rest the collision depends on 1/phi_b only through terms in u = 0, so phi_b
         // acts through F_b alone; theta_b through the collision, F_b and the rebuilt g
         const R Gy = P.ay + P.gbeta * theta_b;
-        w.lphib = P.ax * w.A.Fx + Gy * w.A.Fy;
+        const R lphib = P.ax * w.A.Fx + Gy * w.A.Fy;
         const R lthb = w.A.theta + phi_b * P.gbeta * w.A.Fy;
-        w.H = MacAdj<R>{};
-        const R sw = nee_vjp<R>(m, w.md, P, w.af, w.ag, w.H);
+        MacAdj<R> H{};
+        const R sw = nee_vjp<R>(m, w.md, P, w.af, w.ag, H);
         const bool adiabatic = !((onW && P.iso[0]) || (onE && P.iso[1]) || (onS && P.iso[2]) ||
                                  (onN && P.iso[3]));
-        if (adiabatic) w.H.theta += lthb + sw;    // theta_b = theta_f on an adiabatic side
+        if (adiabatic) H.theta += lthb + sw;    // theta_b = theta_f on an adiabatic side
+        at_wall(H, lphib);
     }
 }
 
 // Value i of the kHandoff values a wall node hands over.
 template <typename R, typename Put>
-__device__ __forceinline__ void adj_hand_over(const AdjNode<R>& w, Put&& put) {
+__device__ __forceinline__ void adj_hand_over(const AdjNode<R>& w, const MacAdj<R>& H, Put&& put) {
 #pragma unroll
     for (int i = 0; i < 9; ++i) put(i, w.af[i]);
 #pragma unroll
     for (int i = 0; i < 5; ++i) put(9 + i, w.ag[i]);
-    put(14, w.H.ux);
-    put(15, w.H.uy);
-    put(16, w.H.ip);
-    put(17, w.H.theta);
+    put(14, H.ux);
+    put(15, H.uy);
+    put(16, H.ip);
+    put(17, H.theta);
     put(18, w.A.P);
 }
 
@@ -415,21 +419,22 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
         const int py = y + (onS ? 1 : 0) - (onN ? 1 : 0);
         pull<R, S>(state, G, px, py, w.f, w.g);
         adj_medium<S, R, PN>(med, G, P, px, py, w);
-        adj_open<R>(P, onW, onE, onS, onN, lout, w,
-                    [&]() { return PN ? R(med[size_t(y) * G.pitch + x]) : P.phi; });
-        if (wall) {
-            adj_hand_over<R>(w, [&](int i, R v) { handoff[i][me] = v; });
-            const bool okx_m = !onW, okx_p = !onE, oky_m = !onS, oky_p = !onN;
-            const bool ok[9] = {true, okx_m, oky_m, okx_p, oky_p, okx_m && oky_m,
-                                okx_p && oky_m, okx_p && oky_p, okx_m && oky_p};
+        adj_open<R>(
+            P, onW, onE, onS, onN, lout, w,
+            [&]() { return PN ? R(med[size_t(y) * G.pitch + x]) : P.phi; },
+            [&](const MacAdj<R>& H, R lphib) {
+                adj_hand_over<R>(w, H, [&](int i, R v) { handoff[i][me] = v; });
+                const bool okx_m = !onW, okx_p = !onE, oky_m = !onS, oky_p = !onN;
+                const bool ok[9] = {true, okx_m, oky_m, okx_p, oky_p, okx_m && oky_m,
+                                    okx_p && oky_m, okx_p && oky_p, okx_m && oky_p};
 #pragma unroll
-            for (int i = 0; i < 9; ++i)
-                if (ok[i]) at(plane(lam_out, i, P1), sl.o[i]) = S(0);
+                for (int i = 0; i < 9; ++i)
+                    if (ok[i]) at(plane(lam_out, i, P1), sl.o[i]) = S(0);
 #pragma unroll
-            for (int i = 0; i < 5; ++i)
-                if (ok[i]) at(plane(lam_out, 9 + i, P1), sl.o[i]) = S(0);
-            at(gphi, og) = gphi0 + double(w.lphib);
-        }
+                for (int i = 0; i < 5; ++i)
+                    if (ok[i]) at(plane(lam_out, 9 + i, P1), sl.o[i]) = S(0);
+                at(gphi, og) = gphi0 + double(lphib);
+            });
     }
     __syncthreads();
     if (!active || wall) return;
@@ -573,6 +578,8 @@ __global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
         const unsigned og = on * unsigned(sizeof(double));
         double gphi0 = 0, gK0 = 0;
         AdjNode<R> w;
+        MacAdj<R> H;   // a wall node's
+        R lphib;
         if (mine) {
             R lout[14];
             if (s == 1) {
@@ -604,12 +611,16 @@ __global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
                 pull<R, S>(X.X[s - 1], G, px, py, w.f, w.g);
                 adj_medium<S, R, PN>(med, G, P, px, py, w);
             }
-            adj_open<R>(P, onW, onE, onS, onN, lout, w, [&]() {
-                return AHEAD || !PN ? own_phi : R(med[size_t(y) * G.pitch + x]);
-            });
-            if (wall) {
+            adj_open<R>(
+                P, onW, onE, onS, onN, lout, w,
+                [&]() { return AHEAD || !PN ? own_phi : R(med[size_t(y) * G.pitch + x]); },
+                [&](const MacAdj<R>& h, R l) {
+                    H = h;
+                    lphib = l;
+                });
+            if (wall) {   // apart here, where in the FP64 form it spills less so (20 B against 36)
                 const int j = onW ? ly : onE ? W + ly : onS ? 2 * W + lx : 3 * W + lx;
-                adj_hand_over<R>(w, [&](int i, R v) { hand[i * 4 * W + j] = v; });
+                adj_hand_over<R>(w, H, [&](int i, R v) { hand[i * 4 * W + j] = v; });
             }
         }
         __syncthreads();   // hand-offs written, the adjoint read
@@ -626,7 +637,7 @@ __global__ __launch_bounds__(kAdjTileThreads) void adjoint_tile_kernel(
                 for (int i = 0; i < 9; ++i) w.af[i] = R(0);
 #pragma unroll
                 for (int i = 0; i < 5; ++i) w.ag[i] = R(0);
-                lphi = w.lphib;
+                lphi = lphib;
             }
             const double gp = gphi0 + double(lphi), gk = gK0 + double(lK);
             if (s < K) {
