@@ -1260,7 +1260,7 @@ lbm_status lbm_grad(lbm_ctx* c, double dJ, void* dJ_dphi, void* dJ_dK) {
         // bank sg % 2, several steps per launch where that pays.
         const int most = with_types(c->p.dtype, [&](auto stt, auto rt) {
             LBM_TYPES(stt, rt)
-            return recompute_steps<S, R>(c->G, c->med);
+            return recompute_steps<S, R>(c->G, c->med, c->p.checkpoint_every);
         });
         const bool by_tiles = with_types(c->p.dtype, [&](auto stt, auto rt) {
             LBM_TYPES(stt, rt)

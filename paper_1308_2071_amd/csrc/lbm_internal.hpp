@@ -63,9 +63,9 @@ hipError_t launch_step(const void* src, void* dst, const void* med, const Geo& G
 // Steps per launch of the time loop that are fastest for this grid and these types
 template <typename S, typename R>
 int default_steps(const Geo& G, bool per_node_medium);
-// Steps per launch of the adjoint's recompute
+// Steps per launch of the adjoint's recompute in segments of so many steps
 template <typename S, typename R>
-int recompute_steps(const Geo& G, bool per_node_medium);
+int recompute_steps(const Geo& G, bool per_node_medium, int segment);
 // k (2, 3, kTileSteps or kTinyTileSteps) steps of the pull layout in one launch from src to dst,
 // each tile of the grid advanced in LDS
 template <typename S, typename R>

@@ -33,9 +33,18 @@ LBM_TILE_KERNEL(tb3_step_kernel)    // three
 LBM_TILE_KERNEL(tb2_step_kernel)    // two
 #undef LBM_TILE_KERNEL
 
+// Wavefronts per SIMD of the form that keeps every state.  Its extra addresses are spilled at the four
+// of 16 x 16 tiles with FP64 arithmetic: 76 bytes per lane with a uniform medium, which takes three
+// instead (256^2 FP64, us per 100 steps of lbm_grad: 1373 / 1243), 28 with a per-node one, which does
+// not (330^2 1763 / 1849).
+template <typename F, typename R, bool PN>
+constexpr int trace_waves() {
+    return !PN && sizeof(R) == 8 && F::K == kTileSteps ? 3 : F::template waves<R>();
+}
+
 // F::K steps that keep every state, step s at dst + (s - 1) * stride.
 template <typename S, typename R, bool PN, typename F>
-__global__ __launch_bounds__(F::NT, (F::template waves<R>())) void tile_trace_kernel(
+__global__ __launch_bounds__(F::NT, (trace_waves<F, R, PN>())) void tile_trace_kernel(
     const S* __restrict__ src, S* __restrict__ dst, size_t stride, const S* __restrict__ med,
     Geo G, Phys<R> P, int tiles_x) {
     const int t = tile_index(), ty = t / tiles_x;
@@ -86,14 +95,23 @@ int default_steps(const Geo& G, bool per_node_medium) {
 }
 
 // Steps per launch of the adjoint's recompute, which runs beside the backward sweep: the default,
-// except for FP64 arithmetic on FP32 storage up to 256^2, where one backward step per launch sets
-// the pace and a tile's work-group holds up the sweep's longer than a single step's does (lbm_grad,
-// us per step, one / several recomputed per launch: 128^2 8.3 / 8.8, 256^2 9.1 / 9.9; FP64, whose
-// sweep takes tiles there, 64^2 9.2 / 8.6, 256^2 13.1 / 10.8).
+// except with FP64 arithmetic on small grids.  On FP32 storage up to 256^2 one backward step per
+// launch sets the pace and a tile's work-group holds up the sweep's longer than a single step's does
+// (lbm_grad, us per step, one / several recomputed per launch: 128^2 8.3 / 8.8, 256^2 9.1 / 9.9; FP64,
+// whose sweep takes tiles there, 64^2 9.2 / 8.6, 256^2 13.1 / 10.8).  Where the default is four steps,
+// segments of up to 40 are recomputed in pairs, on smaller tiles with twice the wavefronts: the
+// sweep waits for a short segment, and four in a launch of two wavefronts per SIMD take longer than
+// two launches (us per 100 steps, pairs / fours / one per launch before there were tiles, segments of
+// 10 and of 100: FP64 uniform 256^2 1104 / 1153 / 1191 and 1318 / 1243 / 1639, FP64 per-node 380^2
+// 1908 / 2101 / 2028 and 2202 / 2290 / 2641, FP32 storage per-node 330^2 1210 / 1335 / 1259 and 1575 /
+// 1473 / 1721).
+constexpr int kPairedSegment = 40;
+
 template <typename S, typename R>
-int recompute_steps(const Geo& G, bool per_node_medium) {
+int recompute_steps(const Geo& G, bool per_node_medium, int segment) {
     if (sizeof(S) == 4 && sizeof(R) == 8 && (long long)G.nx * G.ny <= 256LL * 256) return 1;
-    return default_steps<S, R>(G, per_node_medium);
+    const int k = default_steps<S, R>(G, per_node_medium);
+    return sizeof(R) == 8 && k == kTileSteps && segment <= kPairedSegment ? 2 : k;
 }
 
 // Where two or three steps per launch take their larger tile: from the size on where the launch
@@ -186,7 +204,7 @@ hipError_t launch_tile_trace(const void* src, void* dst, size_t stride, const vo
 
 #define LBM_TILE_INST(S, R)                                                                    \
     template int default_steps<S, R>(const Geo&, bool);                                        \
-    template int recompute_steps<S, R>(const Geo&, bool);                                      \
+    template int recompute_steps<S, R>(const Geo&, bool, int);                                 \
     template void tile_shape<S, R>(const Geo&, int, int*, int*);                               \
     template hipError_t launch_tile_step<S, R>(const void*, void*, const void*, const Geo&,    \
                                                const Phys<R>&, int, hipStream_t);              \
