@@ -119,8 +119,12 @@ int recompute_steps(const Geo& G, bool per_node_medium, int segment) {
 // 28 x 12, FP32: 1024^2 12.1 against 11.3 us per step, 1536^2 23.5 against 22.4 and with a
 // per-node medium 26.0 against 27.3, 4096^2 163 against 182; in FP64 the larger region leaves a
 // compute unit one work-group: 4096^2 358 against 302.  62 x 14 against 30 x 14, FP32: 1024^2
-// 12.8 against 12.2, 4096^2 202 against 224).
-constexpr long long kLargeTileNodes = 1536LL * 1536;
+// 12.8 against 12.2, 4096^2 202 against 224).  The region of 62 x 14 takes 90 KB of LDS with FP64
+// arithmetic on FP32 storage and 147 KB in FP64 (per-node medium), one work-group per compute unit:
+// us per step against 30 x 14, FP32 storage uniform 1540^2 39.6 / 35.4, 4096^2 257 / 236, 8192^2 993 /
+// 901; FP64 per-node 1540^2 71.4 / 69.5, 2048^2 115 / 113, but from there on, where 147 KB of state
+// in flight count for more, 3000^2 235 / 242, 4096^2 418 / 436, 6100^2 928 / 977.
+constexpr long long kLargeTileNodes = 1536LL * 1536, kLargeTileNodes64 = 2500LL * 2500;
 
 template <typename S, typename R, typename F, typename Go>
 auto tile_grid(const Geo& G, Go&& go) {
@@ -140,7 +144,11 @@ auto with_form(const Geo& G, int k, Go&& go) {
         }
         return tile_grid<S, R, Tile3>(G, go);
     }
-    return large ? tile_grid<S, R, Tile2Large>(G, go) : tile_grid<S, R, Tile2>(G, go);
+    if constexpr (sizeof(S) == sizeof(R)) {
+        if (sizeof(R) == 4 ? large : (long long)G.nx * G.ny >= kLargeTileNodes64)
+            return tile_grid<S, R, Tile2Large>(G, go);
+    }
+    return tile_grid<S, R, Tile2>(G, go);
 }
 
 template <typename S, typename R>
