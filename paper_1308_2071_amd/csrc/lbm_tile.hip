@@ -132,20 +132,27 @@ auto tile_grid(const Geo& G, Go&& go) {
     return go(F{}, tiles_x, tiles_x * ((G.ny + F::TY - 1) / F::TY));
 }
 
+// Whether k steps per launch have a form: three do not with FP64 arithmetic on FP32 storage, where four
+// are faster up to 110,000 nodes and two beyond.
+template <typename S, typename R>
+constexpr bool has_form(int k) {
+    return k == 2 || (k == 3 && sizeof(S) == sizeof(R)) || k == kTileSteps || k == kTinyTileSteps;
+}
+
 // Calls go(form, tiles along x, work-groups) with the form that takes k steps on grid G.
 template <typename S, typename R, typename Go>
 auto with_form(const Geo& G, int k, Go&& go) {
-    const bool large = (long long)G.nx * G.ny >= kLargeTileNodes;
+    const long long n = (long long)G.nx * G.ny;
     if (k == kTinyTileSteps) return tile_grid<S, R, Tile8>(G, go);
     if (k == kTileSteps) return tile_grid<S, R, Tile4>(G, go);
-    if (k == 3) {
-        if constexpr (sizeof(R) == 4) {
-            if (large) return tile_grid<S, R, Tile3Large>(G, go);
-        }
-        return tile_grid<S, R, Tile3>(G, go);
-    }
     if constexpr (sizeof(S) == sizeof(R)) {
-        if (sizeof(R) == 4 ? large : (long long)G.nx * G.ny >= kLargeTileNodes64)
+        if (k == 3) {
+            if constexpr (sizeof(R) == 4) {
+                if (n >= kLargeTileNodes) return tile_grid<S, R, Tile3Large>(G, go);
+            }
+            return tile_grid<S, R, Tile3>(G, go);
+        }
+        if (n >= (sizeof(R) == 4 ? kLargeTileNodes : kLargeTileNodes64))
             return tile_grid<S, R, Tile2Large>(G, go);
     }
     return tile_grid<S, R, Tile2>(G, go);
@@ -180,7 +187,7 @@ static hipError_t launch_form(const void* src, void* dst, const void* med, const
 template <typename S, typename R>
 hipError_t launch_tile_step(const void* src, void* dst, const void* med, const Geo& G,
                             const Phys<R>& P, int k, hipStream_t s) {
-    if (k != 2 && k != 3 && k != kTileSteps && k != kTinyTileSteps) return hipErrorInvalidValue;
+    if (!has_form<S, R>(k)) return hipErrorInvalidValue;
     return with_form<S, R>(G, k, [&](auto f, int tiles_x, int nwg) {
         using F = decltype(f);
         return med ? launch_form<S, R, true, F>(src, dst, med, G, P, tiles_x, nwg, s)
@@ -201,12 +208,16 @@ static hipError_t launch_trace(const void* src, void* dst, size_t stride, const 
 template <typename S, typename R>
 hipError_t launch_tile_trace(const void* src, void* dst, size_t stride, const void* med,
                              const Geo& G, const Phys<R>& P, int k, hipStream_t s) {
-    if (k != 2 && k != 3 && k != kTileSteps && k != kTinyTileSteps) return hipErrorInvalidValue;
+    if (!has_form<S, R>(k)) return hipErrorInvalidValue;
     return with_form<S, R>(G, k, [&](auto f, int tiles_x, int nwg) {
         using F = decltype(f);
-        return med ? launch_trace<S, R, true, F>(src, dst, stride, med, G, P, tiles_x, nwg, s)
-                   : launch_trace<S, R, false, F>(src, dst, stride, nullptr, G, P, tiles_x, nwg,
-                                                  s);
+        // grids of eight steps recompute one per launch with FP64 arithmetic on FP32 storage
+        if constexpr (F::K == kTinyTileSteps && sizeof(S) != sizeof(R))
+            return hipErrorInvalidValue;
+        else
+            return med ? launch_trace<S, R, true, F>(src, dst, stride, med, G, P, tiles_x, nwg, s)
+                       : launch_trace<S, R, false, F>(src, dst, stride, nullptr, G, P, tiles_x,
+                                                      nwg, s);
     });
 }
 
