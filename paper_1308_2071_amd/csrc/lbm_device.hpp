@@ -178,8 +178,10 @@ __device__ __forceinline__ double root(double x) {
 // at every node), |v| inside Eq. (21)'s root (a small correction to l0^2) and |u| in Eq. (4)'s
 // Forchheimer term.  FP64 keeps the correctly rounded root.
 __device__ __forceinline__ float rsq_1ulp(float x) { return __builtin_amdgcn_rsqf(x); }
+// root gives -infinity for x < 0 (div_fixup makes it of the NaN), whose reciprocal would pass for an
+// infinite K: a medium value below zero has to show as NaN.
 __device__ __forceinline__ double rsq_1ulp(double x) {
-    return reciprocal(root(x));
+    return x < 0.0 ? double(NAN) : reciprocal(root(x));
 }
 __device__ __forceinline__ float sqrt_1ulp(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double sqrt_1ulp(double x) { return root(x); }
