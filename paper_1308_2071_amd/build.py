@@ -36,13 +36,18 @@ def hipcc() -> str:
 
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
-    tmp = LIB + ".tmp"
-    cmd = [hipcc()] + FLAGS + ["-o", tmp] + srcs
+    return compile_shared(srcs, LIB, verbose)
+
+
+def compile_shared(srcs, out: str, verbose: bool = False) -> str:
+    """A shared library from HIP sources with the library's own flags."""
+    tmp = out + ".tmp"
+    cmd = [hipcc()] + FLAGS + ["-o", tmp] + list(srcs)
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, out)
+    return out
 
 
 if __name__ == "__main__":

@@ -129,12 +129,16 @@ struct Mac {
 // recip, quotient, root: correctly rounded 1/b, a/b and sqrt(x) from the hardware's approximations
 // by Newton steps with fused multiply-adds (Markstein, IBM J. Res. Dev. 34 (1990)), without the
 // scaling that the compiler's expansions spend on operands at the ends of the exponent range,
-// which the step does not have (den >= 1, l0 >= 1/2), and with one reciprocal for both of Eq.
-// (21)'s quotients.  div_fixup puts in the IEEE result for zeros, infinities and NaNs.  In FP32
-// one step each gives 1/b for every mantissa of b and sqrt(x) for every x of two binades (both
-// enumerated on gfx950), and with a correctly rounded reciprocal the quotient is correct wherever
-// its residual does not underflow (|a| above 2^-100); in FP64 2e8 random operands agree with / and
-// sqrt.  Vector instruction slots per node (4 cycles each): FP32 31 to 21, FP64 80 to 55.
+// which the step does not have (den >= 1, l0 >= 1/2; den < 2^65 in FP32 and 2^513 in FP64, beyond
+// which l0^2 overflows), and with one reciprocal for both of Eq. (21)'s quotients.  div_fixup puts in
+// the IEEE result for zeros, infinities and NaNs.  In FP32 one step each gives 1/b for every b in
+// [1, 2^65) and sqrt(x) for every x from 1/4 on, and with a correctly rounded reciprocal the quotient
+// is correct wherever it is normal and its residual does not underflow (|a| above 2^-100); in FP64
+// 2^26 random operands agree with / and sqrt, from 2^-970 on for the root and 2^-960 for the quotient's
+// numerator.  Below, where the residual is subnormal, the root keeps one Newton step's 2^-44: there it
+// is |v| or |u| (velocities below 2^-485) and vanishes beside l0.  tests/test_gpu_rounding.py checks all
+// of this.
+// Vector instruction slots per node (4 cycles each): FP32 31 to 21, FP64 80 to 55.
 __device__ __forceinline__ float recip(float b) {
     const float r = __builtin_amdgcn_rcpf(b);
     return fma(fma(-b, r, 1.0f), r, r);
