@@ -160,7 +160,7 @@ __device__ __forceinline__ R quotient(R a, R b, R r) {
     const R q = a * r;
     return div_special(fma(fma(-b, q, a), r, q), b, a);
 }
-// 1 / b for any b (recip leaves a NaN at b = 0 or infinity)
+// 1 / b for any b (recip leaves a NaN at b = 0 or infinity); a subnormal FP32 b counts as zero
 __device__ __forceinline__ float reciprocal(float b) { return div_special(recip(b), b, 1.0f); }
 __device__ __forceinline__ double reciprocal(double b) { return quotient(1.0, b, recip(b)); }
 __device__ __forceinline__ float root(float x) {
@@ -168,12 +168,16 @@ __device__ __forceinline__ float root(float x) {
     const float g = x * r;
     return div_special(fma(fma(-g, g, x), 0.5f * r, g), 1.0f, x);
 }
-__device__ __forceinline__ double root(double x) {
-    const double r = __builtin_amdgcn_rsq(x);
+// sqrt(x) of a positive finite x from r, the hardware's 1 / sqrt(x)
+__device__ __forceinline__ double root_steps(double x, double r) {
     const double g = x * r, h = 0.5 * r;
     const double e = fma(-h, g, 0.5);
     const double g1 = fma(g, e, g);
-    return div_special(fma(fma(-g1, g1, x), fma(h, e, h), g1), 1.0, x);
+    return fma(fma(-g1, g1, x), fma(h, e, h), g1);
+}
+// x >= 0 (of a negative x div_fixup makes -infinity)
+__device__ __forceinline__ double root(double x) {
+    return div_special(root_steps(x, __builtin_amdgcn_rsq(x)), 1.0, x);
 }
 
 // rsq_1ulp, sqrt_1ulp: in FP32 the hardware reciprocal square root and square root (within
@@ -182,10 +186,15 @@ __device__ __forceinline__ double root(double x) {
 // at every node), |v| inside Eq. (21)'s root (a small correction to l0^2) and |u| in Eq. (4)'s
 // Forchheimer term.  FP64 keeps the correctly rounded root.
 __device__ __forceinline__ float rsq_1ulp(float x) { return __builtin_amdgcn_rsqf(x); }
-// root gives -infinity for x < 0 (div_fixup makes it of the NaN), whose reciprocal would pass for an
-// infinite K: a medium value below zero has to show as NaN.
+// The hardware's value stands for zero and infinity, and a negative operand gives NaN, so that a medium
+// value below zero shows: root's -infinity would pass for an infinite K.  (A comparison of the operand
+// with zero instead of the class test took 2 to 7 % of the one-step kernels on per-node media.)
 __device__ __forceinline__ double rsq_1ulp(double x) {
-    return x < 0.0 ? double(NAN) : reciprocal(root(x));
+    constexpr int kZeroOrInfinity = 0x260;   // class mask: -0, +0, +infinity
+    const double r = __builtin_amdgcn_rsq(x);
+    const double s = root_steps(x, r);
+    const double q = quotient(1.0, s, recip(s));
+    return __builtin_amdgcn_class(x, kZeroOrInfinity) ? r : q;
 }
 __device__ __forceinline__ float sqrt_1ulp(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double sqrt_1ulp(double x) { return root(x); }
