@@ -82,7 +82,7 @@ def parse():
     ap.add_argument("--dtype", default="fp32", choices=("fp32", "fp32_f64"),
                     help="roofline leg: FP32 storage with FP32 or FP64 arithmetic")
     ap.add_argument("--steps-per-launch", type=int, default=0, choices=(0, 1, 2, 3),
-                    help="roofline leg: 0 the library's choice, 1 or 2 forced")
+                    help="roofline leg: 0 the library's choice, 1, 2 or 3 forced")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--no-extras", action="store_true", help="skip batched / adjoint / FP64 legs")
     ap.add_argument("--batch-steps", type=int, default=10000,

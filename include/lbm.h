@@ -101,11 +101,13 @@ typedef struct {
     int32_t checkpoint_every;/* 0: no adjoint tape; C > 0: checkpoint every C steps, lbm_grad on */
     int32_t layout;          /* LBM_LAYOUT_PULL (default) or LBM_LAYOUT_AA                     */
     int32_t steps_per_launch;/* Time steps per launch of the pull layout; the steps of a launch */
-                             /* run on tiles of the lattice in LDS.  0 (default): whichever  */
-                             /* number is fastest for the grid, the type and the medium (8 on */
-                             /* the smallest grids, then 4, 3 or 2).  1: one.  2: two; it     */
-                             /* needs each half of the state (7 of the 14 planes) below 2 GiB */
-                             /* and gives LBM_E_UNSUPPORTED beyond.  3: three; it needs       */
+                             /* run on tiles of the lattice in LDS.  0 (default): by grid,    */
+                             /* type and medium: 8 on the smallest grids, then 4, 3 or 2, the */
+                             /* fastest but on per-node media from 1024^2 to 1536^2 in FP32   */
+                             /* and from 4096^2 in FP64 (2 there, where 3 is faster); what 3  */
+                             /* leave of a step count goes in a launch of 2.  1: one.  2: two; */
+                             /* it needs each half of the state (7 of the 14 planes) below    */
+                             /* 2 GiB and gives LBM_E_UNSUPPORTED beyond.  3: three; it needs */
                              /* LBM_FP32 and the whole state below 2 GiB, else               */
                              /* LBM_E_UNSUPPORTED (the default takes two and three steps     */
                              /* without these limits).  4: four (16 x 16 tiles).  8: eight   */
@@ -249,11 +251,12 @@ lbm_status lbm_batch_workspace_size(int32_t n, const lbm_params* p, size_t* byte
  * (LBM_E_INVAL), a workspace too small (LBM_E_NOMEM) or a failed device call (LBM_E_HIP).
  * tune_cache_path: file where the launch shape picked by the
  * autotuner is cached per (device, dtype, cavity set); NULL disables tuning (default shape: two
- * or three steps per launch).  The autotuner times one and several steps per launch and keeps the fastest;
- * p[0].steps_per_launch = 1 or 2 forces one or two (the other cavities' values are ignored;
- * 2 gives LBM_E_UNSUPPORTED if a cavity's state reaches 2 GiB, a limit the autotuner's choice
- * does not have; 3, 4 and 8, forms of a single cavity, give LBM_E_UNSUPPORTED).  Results are
- * bitwise the same either way. */
+ * or three steps per launch).  A line tuned over another set of tiles is not used, and the batch is
+ * tuned.  The autotuner times one and two steps per launch, from 500,000 nodes on also three and
+ * four, and keeps the fastest; p[0].steps_per_launch = 1 or 2 forces one or two (the other
+ * cavities' values are ignored; 2 gives LBM_E_UNSUPPORTED if a cavity's state reaches 2 GiB, a limit
+ * the autotuner's choice does not have; 3, 4 and 8, forms of a single cavity, give
+ * LBM_E_UNSUPPORTED).  Results are bitwise the same either way. */
 lbm_status lbm_batch_init(lbm_ctx** out, int32_t n, const lbm_params* p,
                           const double* phi_uniform, void* workspace, size_t ws_bytes,
                           void* hip_stream, const char* tune_cache_path);

@@ -77,8 +77,9 @@ __global__ __launch_bounds__(F::NT, (trace_waves<F, R, PN>())) void tile_trace_k
 // smallest of these and 1.1 to 1.9 times on the largest.  FP32 goes from four steps to three between
 // 512^2 and 600 x 520 (uniform 4.65 / 4.42, per-node 4.90 / 4.77; 760 x 520 5.72 / 5.33, 5.96 /
 // 5.65; 800^2 7.70 / 7.36, 8.5 / 8.05).  Per-node media from 1024^2 to 1536^2 in
-// FP32, and from 4096^2 in FP64, keep two steps per launch, which lbm_step_shape has long reported
-// for these grids (three would run 6 to 20 % faster).
+// FP32, and from 4096^2 in FP64, keep the two steps per launch that lbm_step_shape has always reported
+// for these grids, though three are faster there (us per step, two / three: FP32 1024^2 13.0 / 11.3,
+// 1280^2 18.7 / 16.8, 1536^2 30.2 / 24.7; steps_per_launch = 3 asks for them in FP32).
 constexpr long long kTinyTileMaxNodes = 128LL * 128;
 
 template <typename S, typename R>

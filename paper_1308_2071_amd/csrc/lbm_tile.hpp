@@ -23,14 +23,15 @@ namespace lbm {
 // many work-groups a compute unit holds (two buffers and one barrier per step measured the same
 // at best).
 //
-// What bounds it is vector instruction issue: about 330 slots per node and step, times the
-// redundant steps of the halo (1.20 for 28 x 28 tiles advanced three steps, 1.33 for 28 x 12).
-// So the active nodes of a step are dealt to the work-items anew, row by row, and no wavefront
-// runs for a few nodes (one work-item per region node for the whole launch kept three wavefronts
-// per SIMD busy to the end where this mapping needs two, then one), except where whole rows of a
-// region fill wavefronts (kKept below); and the tile is the largest
+// What bounds it is vector instruction issue: 289 slots per node and step in the one-step kernel (FP32),
+// times the redundant steps of the halo (1.15 times the nodes for 28 x 28 tiles advanced three steps,
+// 1.26 for 28 x 12; in whole wavefronts 1.25 and 1.40 as mapped here), plus the LDS: 375 slots per node
+// and step of 28 x 28 tiles with a per-node medium.  So the active nodes of a step are dealt to the
+// work-items anew, row by row, and no wavefront runs for a few nodes (one work-item per region node for
+// the whole launch kept three wavefronts per SIMD busy to the end where this mapping needs two, then
+// one), except where a region's rows are half wavefronts (kKept below); and the tile is the largest
 // whose region still lets a compute unit hold two work-groups, one computing while the other
-// waits for memory or at a barrier.
+// waits for memory or at a barrier (but 62 x 14 in FP64, on grids where its size pays all the same).
 //
 // Each XCD takes one contiguous run of tiles, row by row of the grid, so that a tile's halo is in
 // its XCD's L2 (in launch order, neighbouring tiles on different XCDs: 256^2 FP32 2.75 us per
@@ -105,10 +106,11 @@ __device__ __forceinline__ void tile_steps_body(const S* __restrict__ src, S* __
         cf = c + (onW ? 1 : 0) - (onE ? 1 : 0) + (onS ? W : 0) - (onN ? W : 0);
     };
     // Whether a work-item keeps its node for all K steps instead of being dealt one anew.  A region
-    // 32 nodes wide loses no wavefront by it (two whole rows each, so that rows fall out as they
-    // become inactive), and the place, the walls and the LDS addresses are worked out once: three
-    // steps per launch, us per step, dealt / kept: 28 x 12 FP32 1021 x 509 6.77 / 6.33 and with a
-    // per-node medium 7.08 / 6.84, FP64 11.0 / 10.9; 28 x 28 FP32 uniform 1536^2 21.4 / 20.5,
+    // 32 nodes wide loses little by it (a wavefront holds two whole rows, so that rows fall out as they
+    // become inactive; the second step keeps two half-idle ones: 22 wavefront-steps against 21 for
+    // 28 x 12, 46 against 44 for 28 x 28), and the place, the walls and the LDS addresses are worked
+    // out once: three steps per launch, us per step, dealt / kept: 28 x 12 FP32 1021 x 509 6.77 / 6.33
+    // and with a per-node medium 7.08 / 6.84, FP64 11.0 / 10.9; 28 x 28 FP32 uniform 1536^2 21.4 / 20.5,
     // 3500^2 112.7 / 111.4.  Not with 28 x 28 and a per-node medium (3500^2 125 / 129: the kept
     // values are spilled there), and not for two steps, where only one step would be spared
     // (FP32 storage with FP64 arithmetic, 1024^2, 15.7 / 18.0).
