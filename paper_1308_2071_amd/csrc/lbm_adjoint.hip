@@ -454,7 +454,8 @@ __global__ __launch_bounds__(kAdjThreads) void adjoint_step_kernel(
 // take them: the adjoint of a tile of kAdjSide^2 nodes and its halo stays in LDS from step
 // to step.  On a small grid a backward step is latency, not work: at 256^2 its kernel took 6.8 us
 // (7.8 with the gap to the next), of which the arithmetic of one wavefront per SIMD is a quarter;
-// the launch and the round trip of the adjoint through memory are paid once per launch here.  The dataflow is the forward tile's with the arrows turned round: node x writes slot
+// the launch and the round trip of the adjoint through memory are paid once per launch here.  The
+// dataflow is the forward tile's with the arrows turned round: node x writes slot
 // (i, x - e_i), so a node may take step s when its neighbours took step s - 1, and step 1 covers
 // the tile and kAdjSteps - 1 nodes more on each open side.  A wall node and its inward neighbour
 // need each other within a step, so a region that would stop one node short of a wall takes the

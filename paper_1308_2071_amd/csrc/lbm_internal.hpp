@@ -85,8 +85,9 @@ hipError_t launch_aa_step(void* buf, const void* med, const Geo& G, const Phys<R
 // Work-groups of launch_step, or of launch_aa_step
 int one_step_groups(const Geo& G, size_t elem_bytes, bool aa);
 // layout: the PopLayout form the state is in.  Fields (each may be NULL), and with part (room for
-// kObsParts * kObserveWG + 2 * kNuWG doubles) the kObsOut results at out: the unscaled sums of Eq. (38) at the
-// west and east walls, max |u|, sum f', non-finite flag, min T, max T, max |phi p - rho0 cs^2|.
+// kObsParts * kObserveWG + 2 * kNuWG doubles) the kObsOut results at out: the unscaled sums of Eq.
+// (38) at the west and east walls, max |u|, sum f', non-finite flag, min T, max T, max
+// |phi p - rho0 cs^2|.
 template <typename S, typename R>
 hipError_t launch_observe(const void* src, const void* med, const Geo& G, const Phys<R>& P,
                           int layout, void* ux, void* uy, void* p, void* T, double* part,

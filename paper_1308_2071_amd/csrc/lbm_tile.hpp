@@ -20,8 +20,9 @@ namespace lbm {
 //
 // Steps in between run in place: every active node pulls from LDS into registers, a barrier,
 // every active node writes, a barrier.  One buffer instead of two halves the LDS, which sets how
-// many work-groups a compute unit holds (two buffers and one barrier per step measured the same
-// at best).
+// many work-groups a compute unit holds (two buffers and one barrier per step were no faster where
+// several share a compute unit; on grids of at most one tile per compute unit a sweep of forms showed
+// 8 %, which is not built).
 //
 // What bounds it is vector instruction issue: 289 slots per node and step in the one-step kernel (FP32),
 // times the redundant steps of the halo (1.15 times the nodes for 28 x 28 tiles advanced three steps,
